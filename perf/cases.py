@@ -124,6 +124,16 @@ def _pages(n_blocks):
     return max(n_blocks * 5 // 4, n_blocks + 1)
 
 
+def _weights(case, inp):
+    """One layer's projection [K rows | V rows], gain, shift and bias (None where the width has none)."""
+    d, heads, hd, _, _, norm = WIDTHS[case["width"]]
+    w = inp.normal((2 * heads * hd, d), 0.0, 0.02)
+    gain = inp.normal((d,), 1.0, 0.1)
+    shift = inp.normal((d,), 0.0, 0.05) if norm == "layer" else None
+    bias = inp.normal((2 * heads * hd,), 0.0, 0.05) if norm != "rms" else None
+    return w, gain, shift, bias
+
+
 def _context(case, inp, max_position, num_pages):
     d, heads, hd, theta, style, norm = WIDTHS[case["width"]]
     ctx = hc.Context(hc.ModelDesc(case["layers"], d, heads, heads, hd, BLOCK, max_position, style, theta, 1e-5,
@@ -134,24 +144,19 @@ def _context(case, inp, max_position, num_pages):
         pool = torch.zeros((num_pages, 2, BLOCK, heads, hd), dtype=torch.bfloat16, device="cuda")
         ctx.set_kv_pool(l, pool, num_pages)
         pools.append(pool)
-        w = inp.normal((2 * heads * hd, d), 0.0, 0.02)
-        gain = inp.normal((d,), 1.0, 0.1)
+        w, gain, shift, bias = _weights(case, inp)
         if norm == "rms":
             ctx.set_layer_weights(l, w, gain, stream)
         else:
-            shift = inp.normal((d,), 0.0, 0.05) if norm == "layer" else None
-            ctx.set_layer_weights_affine(l, w, gain, shift, inp.normal((2 * heads * hd,), 0.0, 0.05), stream)
+            ctx.set_layer_weights_affine(l, w, gain, shift, bias, stream)
         torch.cuda.synchronize()       # the weights' buffers are reused from here on
     return ctx, pools
 
 
-def prepare(case, seed):
-    inp = _Inputs(seed)
-    d, heads, hd, _, _, norm = WIDTHS[case["width"]]
+def _places(case, inp):
+    """Positions, block tables and (a batch) row offsets, the pool's pages and the positions there are."""
     path, n = case["path"], case["tokens"]
-    if path == "save":
-        return _prepare_save(case, inp, d)
-    s = {"path": path, "n": n}
+    s = {}
     if path == "ragged":
         lens = lengths(case)
         blocks = [-(-k // BLOCK) for k in lens]
@@ -172,12 +177,24 @@ def prepare(case, seed):
         num_pages = _pages(places * s["blocks"])
         perm = inp.table(places * s["blocks"], num_pages)
         s["table"] = perm[:s["blocks"]].clone()
+        if path == "rows":
+            s["other_table"] = perm[s["blocks"]:].clone()
         s["positions"] = torch.arange(case["offset"], top, dtype=torch.int32, device="cuda")
+    return s, num_pages, top
+
+
+def prepare(case, seed):
+    inp = _Inputs(seed)
+    d, heads, hd, _, _, norm = WIDTHS[case["width"]]
+    path, n = case["path"], case["tokens"]
+    if path == "save":
+        return _prepare_save(case, inp, d)
+    s, num_pages, top = _places(case, inp)
+    s["path"], s["n"] = path, n
     s["ctx"], s["pools"] = _context(case, inp, top, num_pages)
     if path == "rows":
         s["pools"][0].normal_(generator=inp.g)
         s["rows"] = torch.zeros((n, 2 * heads * hd), dtype=torch.bfloat16, device="cuda")
-        s["other_table"] = perm[s["blocks"]:].clone()
     elif path == "store":
         chunks = -(-top // CHUNK)
         s["offset"] = case["offset"]
@@ -266,4 +283,50 @@ def work(case):
 def tolerance(case):
     if case["path"] in ("rows", "save"):
         return "exact"
+    # bf16 results of 32-bit sums over bf16 products: 2.3e-3 off the 64-bit values, of which half is the
+    # rounding of the gain-folded weights and half that of the results
     return {"rel": 0.01, "max": 0.05}
+
+
+# ---- the same in 64 bits ---------------------------------------------------------------------
+def exact(case, seed):
+    """What `run` returns, in plain torch with 64-bit inputs, sums and results: normalisation,
+    K|V projection, rotation of K, rows into their pages."""
+    path, n = case["path"], case["tokens"]
+    if path in ("rows", "save"):       # bytes that are moved
+        return None
+    inp = _Inputs(seed)
+    d, heads, hd, theta, style, norm = WIDTHS[case["width"]]
+    s, num_pages, top = _places(case, inp)
+    weights = [_weights(case, inp) for _ in range(case["layers"])]
+    pos = s["positions"].long()
+    if path == "ragged":
+        context = torch.repeat_interleave(torch.arange(s["contexts"], device="cuda"), s["cu"].long().diff())
+        page = s["table"][context, pos // BLOCK].long()
+    else:
+        page = s["table"][pos // BLOCK].long()
+    half = torch.arange(hd // 2, dtype=torch.float64, device="cuda")
+    angle = pos.double()[:, None] * theta ** (-2 * half / hd)
+    cos, sin = angle.cos()[:, None], angle.sin()[:, None]
+    out = []
+    for w, gain, shift, bias in weights:
+        x = inp.hidden(top if path == "store" else n, d, norm)[-n:].double()
+        if norm == "layer":
+            x -= x.mean(1, keepdim=True)
+        x *= (x.square().mean(1, keepdim=True) + 1e-5).rsqrt()
+        x *= gain.double()
+        if shift is not None:
+            x += shift.double()
+        y = x @ w.double().t()
+        if bias is not None:
+            y += bias.double()
+        k, v = y.view(n, 2, heads, hd).unbind(1)
+        if style != 2:
+            a, b = (k[..., :hd // 2], k[..., hd // 2:]) if style == 0 else (k[..., 0::2], k[..., 1::2])
+            a, b = a * cos - b * sin, b * cos + a * sin
+            k = torch.cat([a, b], -1) if style == 0 else torch.stack([a, b], -1).flatten(-2)
+        pool = torch.zeros((num_pages, 2, BLOCK, heads, hd), dtype=torch.float64, device="cuda")
+        pool[page, 0, pos % BLOCK] = k
+        pool[page, 1, pos % BLOCK] = v
+        out.append(pool)
+    return out
