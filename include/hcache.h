@@ -392,10 +392,13 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * an unsplit launch (fp32 summation order).  Split launches of one context are ordered after
  * each other through an event, whatever their streams.  mode 0: never split.  mode 2: split
  * whenever the shape allows it (tests and measurements).  Launches over several layers
- * (hc_restore_kv_layers) never split. */
+ * (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
+ * a kernel of its own when that is faster than whole or split tiles (up to 500 tokens or so
+ * with few heads, 50 with many); its workgroups' waves share the d_model loop, so the same holds
+ * for its results; it uses no workspace and one launch. */
 hc_status hc_set_split(hc_ctx* ctx, int32_t mode);
-/* Host-side view of that decision for a layer of d_model, d_kv and n_tok under `mode` (no
- * device work): out_plan[8] = { 1 if split else 0, feature tiles, token tiles, token tiles
+/* Host-side view of the split of a layer of d_model, d_kv and n_tok under `mode` when it goes to the
+ * 256 x 256 tiles (no device work): out_plan[8] = { 1 if split else 0, feature tiles, token tiles, token tiles
  * computed whole, tiles that are split, workgroups per split tile, workgroup slots of the whole
  * tiles (first in the grid; padding slots included), workgroups of the finishing launch }. */
 hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t mode, int32_t* out_plan);

@@ -1,5 +1,7 @@
-// One-time kernels: weight packing (per layer) and the RoPE (cos, sin) table (per context).
+// One-time kernels: weight packing (per layer) and the RoPE (cos, sin) table (per context); the
+// byte movers; the translation unit of the few-token restoration kernel.
 #include "hcache_internal.h"
+#include "restore_small.inc"
 
 namespace hc {
 
@@ -19,9 +21,10 @@ namespace hc {
 //   pair offsets 8*q .. 8*q + 7 (one 16-byte store).
 // Value: bf16( float(W[logical row][c]) * float(gamma[c]) ), one rounding.
 // Memory order: tiles of 256 physical rows x 32 channels, [row tile][channel tile][row][32],
-// each tile 16 KiB and laid out exactly as the restoration kernel wants it in LDS (the four
-// 16-byte chunks of a row XOR-swizzled by swz_w), so a tile is fetched with fully
-// contiguous 1 KiB wave loads.
+// each tile 16 KiB and laid out in matrix-op fragment order: per 16-row block the four 16-byte
+// chunks of the 32 channels, and for each chunk the block's 16 rows.  A fragment (lane l16 of
+// quarter q4 takes chunk q4 of row l16) is thus 1 KiB with 16 bytes per lane in lane order:
+// one fully coalesced load, or one conflict-free LDS read.
 __device__ __forceinline__ int logical_row(int p, int d_kv, int d_kv_pad, int hd, int style) {
   const int part = (p >> 6) & 1;                          // K and V groups alternate
   const int grp = p >> 7;
@@ -55,7 +58,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t* __res
     const uint16_t out = src >= 0 ? fold_gain(wkv[(size_t)src * d_model + c], gamma[c]) : (uint16_t)0;
     const int tile_f = p >> 8, r = p & 255, kt = c >> 5, chunk = (c >> 3) & 3, e = c & 7;
     const size_t tile = (size_t)tile_f * (d_model >> 5) + kt;
-    wpack[tile * (kWTileBytes / 2) + r * 32 + ((chunk ^ swz_w(r)) << 3) + e] = out;
+    wpack[tile * (kWTileBytes / 2) + (r >> 4) * 512 + chunk * 128 + (r & 15) * 8 + e] = out;
   }
 }
 

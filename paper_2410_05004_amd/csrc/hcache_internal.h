@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <map>
@@ -25,15 +26,11 @@ constexpr int kTileT = 256;       // tokens per workgroup
 constexpr int kTileK = 32;        // d_model slice per main-loop step
 constexpr int kWTileBytes = kTileF * kTileK * 2;   // one packed weight tile: 256 rows x 64 bytes
 
-// LDS placement of 16-byte chunks (XOR swizzles; they make the ds_read_b128 fragment reads
-// bank-conflict free).  Weight tiles have 64-byte rows (4 chunks): chunk c of row r sits at
-// position c ^ swz_w(r).  Activation super-tiles have 128-byte rows (8 chunks): chunk c of
-// row r sits at position c ^ swz_x(r).  The pack kernel bakes swz_w into the global layout.
-// A fragment read takes 16 consecutive rows per lane quarter, quarter q reading chunk q (+ 4
-// for odd steps of the activations); both functions were checked with the bank-conflict
-// counter (0 conflicts) -- (row >> 2) & 3 for the weights gives two-way conflicts with this
-// access shape.
-__host__ __device__ inline int swz_w(int row) { return (row >> 1) & 3; }
+// LDS placement of the activations' 16-byte chunks: super-tiles have 128-byte rows (8 chunks),
+// chunk c of row r sits at position c ^ swz_x(r).  A fragment read takes 16 consecutive rows per
+// lane quarter, quarter q reading chunk q (+ 4 for odd steps), and is bank-conflict free
+// (checked with the bank-conflict counter).  The packed weights need no swizzle: they are
+// stored, and staged, in fragment order.
 __host__ __device__ inline int swz_x(int row) { return (row >> 1) & 7; }
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
@@ -156,6 +153,49 @@ __host__ __device__ inline void split_range(int nm, int n, int s, int& m_begin, 
   m_end = (int)((long)nm * (s + 1) / n);
 }
 
+// Few tokens (restore_small.hip): 32 packed rows x 16 nb tokens per workgroup, no cross-workgroup
+// sums.  Returns the nb of 1..4 to launch with, or 0 to leave the layer to the 256 x 256 tiles.
+//
+// A launch is as long as the busiest CU takes to stream its operands: 64 bytes per channel for the
+// rows and 32 nb for the tokens, per workgroup; up to nb = 2 two workgroups share a CU, so
+// their load evens out.  Token sweeps (d_model 1024 .. 8192, 8 .. 56 heads, 5 .. 512 tokens) fit
+// 3.5 us + the hypotenuse of that (2.85e-5 us per channel and unit of 32 + 16 nb) and the time
+// the weights take from memory (5.4 MB/us), to 20 %.  The other side of the comparison is what
+// plan_split's figures give for the tiles, with the workspace traffic of the live token blocks only.
+// Below d_model 1024 the large tiles' workgroups take too short for a second order of sums to
+// be worth having: there every launch adds a token's channels up in the same order.
+// Measured, this kernel against the tiles: 16 tokens 10.2 / 24.8 us (d_model 4096, 8 heads),
+// 18.7 / 34.5 (32 heads), 29.3 / 41.7 (5120, 40 heads); 64 tokens 10.4 / 26.6, 23.6 / 36.6, 40.6 /
+// 43.9; 256 tokens 15.9 / 34.1, 61.3 / 47.7, 88.0 / 59.5.
+constexpr int kSmallMinModel = 1024;
+inline int plan_small(int d_kv, int d_model, int n_tok) {
+  if (d_model < kSmallMinModel) return 0;
+  const int units = 2 * d_kv / 32;
+  int nb = 0;
+  float best = 0.f;
+  for (int b = 1; b <= 4; ++b) {
+    const float wgs = (float)units * ((n_tok + 16 * b - 1) / (16 * b)) / kChipCUs;
+    const float rounds = b <= 2 ? (wgs > 1.f ? wgs : 1.f) : ceilf(wgs);
+    const float c = rounds * (32 + 16 * b);
+    if (b == 1 || c < best) { best = c; nb = b; }
+  }
+  const float weights_us = 4.f * d_kv * d_model / 5.4e6f, stream_us = 2.85e-5f * d_model * best;
+  const float small_us = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
+
+  const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF, nt = (n_tok + kTileT - 1) / kTileT, nm = d_model / (2 * kTileK);
+  float tiles_us = kWholeStepUs * nm * ((nf * nt + kChipCUs - 1) / kChipCUs);
+  SplitPlan sp;
+  TileGrid g;
+  if (plan_split(nf, nt, nm, false, sp, g)) {
+    const int rest = n_tok - sp.nt_main * kTileT;        // tokens of the split tiles
+    const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
+    float loop = kSplitStepUs * nm / sp.n_split;
+    if (loop < weights_us) loop = weights_us;
+    tiles_us = kWholeStepUs * nm * (nf * nt / kChipCUs) + loop + kSplitSlotUs * sp.n_tail * sp.n_split * live + kSplitFixedUs;
+  }
+  return small_us < tiles_us ? nb : 0;
+}
+
 // Arguments of one restoration launch (device pointers unless noted).
 struct RestoreArgs {
   const uint16_t* hidden;        // bf16 [n_tok, d_model]
@@ -215,6 +255,12 @@ struct LayerBatch {
 // Launchers implemented in the .hip files.  All are asynchronous on `stream`.
 // `batch` null: one layer from `a`; else n_layers <= kMaxLayersPerLaunch layers in one launch.
 hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream);
+hipError_t launch_restore_small(const RestoreArgs& a, int nb, hipStream_t stream);
+// The nb a single-layer launch of `a` goes to the few-token kernel with, or 0: only where the
+// order of the sums may depend on the token count (split launches allowed and not asked for).
+inline int restore_small_nb(const RestoreArgs& a) {
+  return a.split_ws && !a.split_force && a.n_tok > 0 ? plan_small(a.d_kv, a.d_model, a.n_tok) : 0;
+}
 // Whether a single-layer launch of `a` takes the split plan (a.split_ws set and plan_split agrees).
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main);
 hipError_t launch_pack_weights(const uint16_t* wkv, const uint16_t* gamma, uint16_t* wpack,

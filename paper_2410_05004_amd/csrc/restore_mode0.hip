@@ -19,12 +19,16 @@ hipError_t configure_kernels() {
 }
 
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main) {
-  if (!a.split_ws || a.n_tok <= 0) return false;
+  if (!a.split_ws || a.n_tok <= 0 || restore_small_nb(a)) return false;
   return plan_split(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, a.d_model / (2 * kTileK), a.split_force != 0, sp, g_main);
 }
 
 hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream) {
   if (a.n_tok <= 0) return hipSuccess;
+  if (!batch) {
+    const int nb = restore_small_nb(a);
+    if (nb) return launch_restore_small(a, nb, stream);
+  }
   TileGrid g;
   SplitPlan sp;
   const SplitPlan* use_split = nullptr;

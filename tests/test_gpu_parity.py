@@ -203,6 +203,44 @@ def test_split_and_unsplit_launches_agree_on_random_shapes(hc, torch):
               f"{plan['n_split']}; {np.mean(a[m] == b[m]):.4f} of the values bit-identical", flush=True)
 
 
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,style,norm", [
+    (1024, 2, 64, 1, 0, 0),        # one token; two supersteps of the loop per wave
+    (1088, 3, 64, 16, 1, 0),       # 17 supersteps over eight waves; padded K/V parts
+    (4096, 8, 128, 17, 0, 0),
+    (1600, 2, 192, 33, 1, 0),      # pair groups that straddle the tile's heads
+    (2048, 16, 128, 49, 0, 0),
+    (1024, 40, 128, 50, 2, 0),     # several workgroups per CU
+    (2048, 1, 256, 130, 0, 0),
+    (4096, 8, 128, 201, 0, 0),     # four blocks of tokens per workgroup, ragged last one
+    (1472, 5, 128, 47, 0, 1),      # LayerNorm
+    (4096, 4, 64, 240, 2, 1),
+])
+def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm):
+    """Layers that the few-token kernel takes, at the edges of its token blocks and loop shares:
+    against the CPU model of the arithmetic (RMSNorm), and against the kernel of whole tiles
+    within one bf16 step, or, for values that are small because their terms cancel, 2^-9 of the
+    RMS of all values (the order of fp32 additions is what differs)."""
+    rng = np.random.default_rng([77, d_model, n_kv, hd, n_tok, style, norm])
+    case = gh.LayerCase(rng, d_model, n_kv, hd, n_tok)
+    B, offset = 16, 40
+    n_blocks = (offset + n_tok + B - 1) // B
+    num_pages = n_blocks + 3
+    bt = rng.permutation(num_pages)[:n_blocks].astype(np.int32)
+    pos = (offset + rng.permutation(n_tok)).astype(np.int32)
+    desc = gh.make_desc(hc, n_layers=1, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd,
+                        block_size=B, max_position=offset + n_tok, rope_style=style, norm_kind=norm)
+    bits, flags = run_single(hc, torch, case, desc, pos, bt, num_pages)
+    whole, flags0 = run_single(hc, torch, case, desc, pos, bt, num_pages, split=0)
+    assert flags == 0 and flags0 == 0
+    if norm == 0:
+        gh.assert_close_to_model(bits, gh.model_pool(desc, case.x, case.gamma, case.wkv, pos, bt, num_pages))
+    m = whole != gh.SENTINEL
+    assert np.array_equal(bits != gh.SENTINEL, m) and m.sum() == 2 * n_tok * n_kv * hd
+    fa, fb = syn.bf16_bits_to_f64(bits[m]), syn.bf16_bits_to_f64(whole[m])
+    step = np.maximum(np.abs(fa), np.abs(fb)) * 2.0 ** -7
+    assert np.all(np.abs(fa - fb) <= np.maximum(step, np.sqrt(np.mean(fb * fb)) * 2.0 ** -9))
+
+
 def test_block_sizes(hc, torch):
     for B in (8, 32):
         rng = np.random.default_rng([5, B])
