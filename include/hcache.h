@@ -395,7 +395,9 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
  * a kernel of its own when that is faster than whole or split tiles (up to 500 tokens or so
  * with few heads, 50 with many); its workgroups' waves share the d_model loop, so the same holds
- * for its results; it uses no workspace and one launch. */
+ * for its results; it uses no workspace and one launch.  In modes 0 and 1 launches that whole tiles
+ * fill badly (a short context, a device partly idle) go to tiles of 128 features x 64..320 tokens,
+ * whose results are those of the unsplit 256 x 256 tiles bit for bit. */
 hc_status hc_set_split(hc_ctx* ctx, int32_t mode);
 /* Host-side view of the split of a layer of d_model, d_kv and n_tok under `mode` when it goes to the
  * 256 x 256 tiles (no device work): out_plan[8] = { 1 if split else 0, feature tiles, token tiles, token tiles

@@ -153,8 +153,8 @@ __host__ __device__ inline void split_range(int nm, int n, int s, int& m_begin, 
   m_end = (int)((long)nm * (s + 1) / n);
 }
 
-// Few tokens (restore_small.hip): 32 packed rows x 16 nb tokens per workgroup, no cross-workgroup
-// sums.  Returns the nb of 1..4 to launch with, or 0 to leave the layer to the 256 x 256 tiles.
+// Few tokens (restore_small.inc): 32 packed rows x 16 nb tokens per workgroup, no cross-workgroup
+// sums (nb 1..4).
 //
 // A launch is as long as the busiest CU takes to stream its operands: 64 bytes per channel for the
 // rows and 32 nb for the tokens, per workgroup; up to nb = 2 two workgroups share a CU, so
@@ -168,32 +168,86 @@ __host__ __device__ inline void split_range(int nm, int n, int s, int& m_begin, 
 // 18.7 / 34.5 (32 heads), 29.3 / 41.7 (5120, 40 heads); 64 tokens 10.4 / 26.6, 23.6 / 36.6, 40.6 /
 // 43.9; 256 tokens 15.9 / 34.1, 61.3 / 47.7, 88.0 / 59.5.
 constexpr int kSmallMinModel = 1024;
-inline int plan_small(int d_kv, int d_model, int n_tok) {
-  if (d_model < kSmallMinModel) return 0;
-  const int units = 2 * d_kv / 32;
-  int nb = 0;
-  float best = 0.f;
-  for (int b = 1; b <= 4; ++b) {
-    const float wgs = (float)units * ((n_tok + 16 * b - 1) / (16 * b)) / kChipCUs;
-    const float rounds = b <= 2 ? (wgs > 1.f ? wgs : 1.f) : ceilf(wgs);
-    const float c = rounds * (32 + 16 * b);
-    if (b == 1 || c < best) { best = c; nb = b; }
-  }
-  const float weights_us = 4.f * d_kv * d_model / 5.4e6f, stream_us = 2.85e-5f * d_model * best;
-  const float small_us = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
 
-  const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF, nt = (n_tok + kTileT - 1) / kTileT, nm = d_model / (2 * kTileK);
-  float tiles_us = kWholeStepUs * nm * ((nf * nt + kChipCUs - 1) / kChipCUs);
-  SplitPlan sp;
-  TileGrid g;
-  if (plan_split(nf, nt, nm, false, sp, g)) {
-    const int rest = n_tok - sp.nt_main * kTileT;        // tokens of the split tiles
-    const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
-    float loop = kSplitStepUs * nm / sp.n_split;
-    if (loop < weights_us) loop = weights_us;
-    tiles_us = kWholeStepUs * nm * (nf * nt / kChipCUs) + loop + kSplitSlotUs * sp.n_tail * sp.n_split * live + kSplitFixedUs;
+// Tiles of 128 rows x 64 nb tokens (restore_mid.inc).  They add a token's channels up in the order of the
+// unsplit 256 x 256 tiles, so results do not depend on which of the two a launch takes.
+//
+// Cost of a round of 256 workgroups (512 for nb = 1 beyond the first 256: two share a CU), from token
+// sweeps of d_model 256 .. 8192, 8 .. 56 heads: kMidStepUs per 64 channels and 3 + 0.7 nb for
+// prologue and epilogue; a round of the large tiles takes 1.5 and 5.  Launches of several layers run
+// their rounds into each other (fractions of a round count) and read every layer's weights from memory:
+// the hypotenuse with that time fits both kernels to 15 %, but for nb = 5, whose ring of two stages
+// does not cover the memory's latency (300 tokens, 8 layers of 5120 onto 10240: 368 us against 308), and
+// which LayerNorm's extra matrix ops make slower than the large tiles (558 tokens of 7168 onto 14336:
+// 167 us against 153).  A single layer takes nb = 1 up to 512 workgroups only: beyond, the pairs lose step and
+// with it the L2 (those 558 tokens, 1008 workgroups: 259 us).  The figures are good to a few percent, so these tiles have to promise 5 %.
+// Measured, these tiles against the large ones (whole or split): one layer of 4096 onto 2048, 800 tokens
+// 25.5 / 44.0 us, 4000 tokens 62.9 / 90.9, 6000 tokens 98.4 / 99.6 (not taken); 5120 onto 10240, 300
+// tokens 52.8 / 62.9, 900 99.0 / 120, 1200 147 / 123 (not taken); 32 layers of 4096 onto 2048, 40
+// tokens 111 / 126, 256 tokens 181 / 147 (not taken).
+constexpr float kMidStepUs[6] = {0.f, 0.40f, 0.58f, 0.77f, 0.98f, 1.20f};
+constexpr float kMidPairStepUs = 0.65f;                  // nb = 1, two workgroups on a CU
+constexpr float kTileFixedUs = 5.f, kWeightsUsPerByte = 1.f / 5.4e6f;
+
+struct Route {
+  enum Kind { kTiles, kSmall, kMid } kind;
+  int nb;
+};
+// Which kernel a launch of n_layers layers takes.  `free_order`: the order of the sums may depend on the
+// token count (split launches allowed); the few-token kernel and split plans need it.
+inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool layer_norm, bool free_order) {
+  const int nm = d_model / (2 * kTileK);
+  const float weights_us = 4.f * d_kv * d_model * kWeightsUsPerByte;
+  const float all_weights_us = weights_us * n_layers;
+  Route best_route{Route::kTiles, 0};
+
+  // the 256 x 256 tiles, whole or split
+  const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF, nt = (n_tok + kTileT - 1) / kTileT;
+  const float tiles = (float)nf * nt * n_layers / kChipCUs;
+  float best;
+  if (n_layers > 1) {
+    const float t = (kWholeStepUs * nm + kTileFixedUs) * (tiles > 1.f ? tiles : 1.f);
+    best = sqrtf(t * t + all_weights_us * all_weights_us);
+  } else {
+    best = (kWholeStepUs * nm + kTileFixedUs) * ceilf(tiles);
+    SplitPlan sp;
+    TileGrid g;
+    if (free_order && plan_split(nf, nt, nm, false, sp, g)) {
+      const int rest = n_tok - sp.nt_main * kTileT;      // tokens of the split tiles
+      const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
+      float loop = 1.1f * kSplitStepUs * nm / sp.n_split;   // with most CUs busy
+      if (loop < weights_us) loop = weights_us;
+      best = kWholeStepUs * nm * (nf * nt / kChipCUs) + loop + kSplitSlotUs * sp.n_tail * sp.n_split * live + kSplitFixedUs + kTileFixedUs;
+    }
   }
-  return small_us < tiles_us ? nb : 0;
+
+  const int groups = d_kv / kPairGroup;
+  for (int b = 1; b <= (n_layers > 1 || layer_norm ? 4 : 5); ++b) {
+    const float wgs = (float)groups * ((n_tok + 64 * b - 1) / (64 * b)) * n_layers / kChipCUs;
+    const bool pair = b == 1 && wgs > 1.f;
+    if (pair && n_layers == 1 && wgs > 2.f) continue;
+    float rounds = pair ? wgs / 2 : wgs;
+    rounds = n_layers > 1 ? (rounds > 1.f ? rounds : 1.f) : ceilf(rounds);
+    float t = 1.05f * rounds * ((pair ? kMidPairStepUs : kMidStepUs[b]) * nm + 3.f + 0.7f * b);
+    if (n_layers > 1) t = sqrtf(t * t + all_weights_us * all_weights_us);
+    if (t < best) { best = t; best_route = Route{Route::kMid, b}; }
+  }
+
+  if (n_layers == 1 && free_order && d_model >= kSmallMinModel) {
+    const int units = 2 * d_kv / 32;
+    int nb = 0;
+    float cost = 0.f;
+    for (int b = 1; b <= 4; ++b) {
+      const float wgs = (float)units * ((n_tok + 16 * b - 1) / (16 * b)) / kChipCUs;
+      const float rounds = b <= 2 ? (wgs > 1.f ? wgs : 1.f) : ceilf(wgs);
+      const float c = rounds * (32 + 16 * b);
+      if (b == 1 || c < cost) { cost = c; nb = b; }
+    }
+    const float stream_us = 2.85e-5f * d_model * cost;
+    const float t = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
+    if (t < best) { best = t; best_route = Route{Route::kSmall, nb}; }
+  }
+  return best_route;
 }
 
 // Arguments of one restoration launch (device pointers unless noted).
@@ -255,13 +309,17 @@ struct LayerBatch {
 // Launchers implemented in the .hip files.  All are asynchronous on `stream`.
 // `batch` null: one layer from `a`; else n_layers <= kMaxLayersPerLaunch layers in one launch.
 hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream);
+// Tiles of 128 packed rows x 64 nb tokens (nb 1..5), one launch; `batch` as in launch_restore.
+hipError_t launch_restore_mid(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
 hipError_t launch_restore_small(const RestoreArgs& a, int nb, hipStream_t stream);
-// The nb a single-layer launch of `a` goes to the few-token kernel with, or 0: only where the
-// order of the sums may depend on the token count (split launches allowed and not asked for).
-inline int restore_small_nb(const RestoreArgs& a) {
-  return a.split_ws && !a.split_force && a.n_tok > 0 ? plan_small(a.d_kv, a.d_model, a.n_tok) : 0;
+// The kernel a launch of n_layers layers of `a` takes.  A context that asks for split launches gets the
+// 256 x 256 tiles.
+inline Route restore_route(const RestoreArgs& a, int n_layers) {
+  if (a.split_force) return Route{Route::kTiles, 0};
+  return plan_route(a.d_kv, a.d_model, a.n_tok, n_layers, a.mode == 2, a.split_ws != nullptr);
 }
-// Whether a single-layer launch of `a` takes the split plan (a.split_ws set and plan_split agrees).
+// Whether a single-layer launch of `a` takes the split plan (a.split_ws set, routed to the tiles, and
+// plan_split agrees).
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main);
 hipError_t launch_pack_weights(const uint16_t* wkv, const uint16_t* gamma, uint16_t* wpack,
                                int d_model, int d_kv, int head_dim, int rope_style,
@@ -273,6 +331,7 @@ hipError_t launch_pack_affine(const uint16_t* wkv, const uint16_t* gamma, const 
                               int head_dim, int rope_style, hipStream_t stream);
 hipError_t launch_rope_table(float2* table, int max_position, int head_dim, double theta,
                              hipStream_t stream);
+hipError_t configure_mid();
 hipError_t configure_kernels();   // one-time function attributes (dynamic LDS size)
 // Measurement only: chip-wide matrix-op rate (TFLOP/s, as if all 256 CUs were busy) inside
 // the busy windows of a duty-cycled burst pattern; allocates and frees its own buffers and

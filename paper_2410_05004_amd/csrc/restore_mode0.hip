@@ -15,20 +15,21 @@ hipError_t configure_kernels() {
   if (e != hipSuccess) return e;
   e = configure_mode1();
   if (e != hipSuccess) return e;
-  return configure_mode2();
+  e = configure_mode2();
+  if (e != hipSuccess) return e;
+  return configure_mid();
 }
 
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main) {
-  if (!a.split_ws || a.n_tok <= 0 || restore_small_nb(a)) return false;
+  if (!a.split_ws || a.n_tok <= 0 || restore_route(a, 1).kind != Route::kTiles) return false;
   return plan_split(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, a.d_model / (2 * kTileK), a.split_force != 0, sp, g_main);
 }
 
 hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream) {
   if (a.n_tok <= 0) return hipSuccess;
-  if (!batch) {
-    const int nb = restore_small_nb(a);
-    if (nb) return launch_restore_small(a, nb, stream);
-  }
+  const Route route = restore_route(a, batch ? n_layers : 1);
+  if (route.kind == Route::kMid) return launch_restore_mid(a, route.nb, batch, n_layers, stream);
+  if (!batch && route.kind == Route::kSmall) return launch_restore_small(a, route.nb, stream);
   TileGrid g;
   SplitPlan sp;
   const SplitPlan* use_split = nullptr;

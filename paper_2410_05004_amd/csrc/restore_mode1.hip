@@ -1,5 +1,7 @@
-// RMSNorm + projection bias instantiations of the restoration kernel.
+// RMSNorm + projection bias instantiations of the restoration kernel; the translation unit of the tiles
+// of 128 rows.
 #include "restore_kernel.inc"
+#include "restore_mid.inc"
 
 namespace hc {
 

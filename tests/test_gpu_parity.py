@@ -241,6 +241,84 @@ def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm):
     assert np.all(np.abs(fa - fb) <= np.maximum(step, np.sqrt(np.mean(fb * fb)) * 2.0 ** -9))
 
 
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm", [
+    (64, 1, 64, 1, 2, 0, "rms"),           # one token, one superstep of the loop, one workgroup
+    (256, 4, 64, 65, 3, 1, "rms"),         # one token in the second tile
+    (576, 3, 192, 130, 2, 0, "bias"),      # padded K/V parts, pair groups that straddle the packed tile's halves
+    (640, 43, 128, 140, 1, 0, "rms"),      # two token blocks per wave (one layer)
+    (128, 42, 128, 193, 1, 1, "layer"),
+    (64, 103, 64, 257, 1, 2, "bias"),      # three
+    (192, 43, 128, 387, 1, 0, "layer"),    # four
+    (512, 43, 128, 517, 1, 0, "rms"),      # five
+    (768, 43, 128, 77, 3, 0, "layer"),     # two token blocks per wave, several layers
+    (64, 77, 64, 140, 3, 1, "rms"),        # three
+    (192, 67, 64, 205, 3, 0, "bias"),      # four
+])
+def test_mid_tiles_equal_whole_tiles(hc, torch, d_model, n_kv, hd, n_tok, layers, style, norm):
+    """Shapes that go to tiles of 128 rows x 64..320 tokens, at the edges of the tiles and rings: layer
+    by layer, all layers at once and as a ragged batch, with two rows whose position and page are
+    invalid, bit for bit the 256 x 256 tiles' results and flags (below d_model 1024 a context that asks
+    for split launches gets whole tiles: nothing can be split)."""
+    torch.manual_seed(d_model * 7919 + n_tok)
+    rows, B, offset = 2 * n_kv * hd, 16, 40
+    desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                        max_position=offset + n_tok, rope_style=style, norm_kind=1 if norm == "layer" else 0)
+    assert hc.diag_split_plan(d_model, n_kv * hd, n_tok, 2)["split"] == 0
+    ctx, s = hc.Context(desc), gh.stream_handle()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    n_blocks = (offset + n_tok + B - 1) // B
+    num_pages = n_blocks + 3
+    keep, pools, xs = [], [], []
+    for l in range(layers):
+        w, gain = torch.randn((rows, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+        shift = 0.1 * torch.randn(d_model, **bf) if norm == "layer" else None
+        bias = 0.1 * torch.randn(rows, **bf) if norm != "rms" else None
+        keep += [w, gain, shift, bias]
+        if norm == "rms":
+            ctx.set_layer_weights(l, w, gain, s)
+        else:
+            ctx.set_layer_weights_affine(l, w, gain, shift, bias, s)
+        pools.append(gh.new_pool(num_pages, B, n_kv, hd))
+        ctx.set_kv_pool(l, pools[l], num_pages)
+        xs.append(torch.randn((n_tok, d_model), **bf) + 0.25)
+    pos = torch.arange(offset, offset + n_tok, dtype=torch.int32, device="cuda")
+    table = torch.randperm(num_pages, device="cuda")[:n_blocks].to(torch.int32)
+    if n_tok > 2:
+        pos[n_tok // 2] = offset + n_tok                  # past max_position
+        table[-1] = num_pages                             # not a page of the pool
+    cut = n_tok // 3
+    cu = torch.tensor([0, cut, n_tok], dtype=torch.int32, device="cuda")
+    tables = torch.stack([table, table])
+
+    def ragged(l):
+        ctx.restore_kv_ragged(l, xs[l], pos, n_tok, cu, 2, tables, n_blocks, s)
+
+    def single(l):
+        ctx.restore_kv(l, xs[l], pos, n_tok, table, n_blocks, s)
+
+    def outcome(mode, call):
+        ctx.set_split(mode)
+        for p in pools:
+            p.view(torch.int16).fill_(np.array(gh.SENTINEL, dtype=np.uint16).view(np.int16).item())
+        if call is None:
+            ctx.restore_kv_layers(0, xs, pos, n_tok, table, n_blocks, s)
+        else:
+            for l in range(layers):
+                call(l)
+        flags = ctx.poll_device_error(s)
+        return flags, [gh.pool_bits(p) for p in pools]
+
+    flags, want = outcome(2, single)
+    assert (flags != 0) == (n_tok > 2)
+    assert all(0 < (b != gh.SENTINEL).sum() <= n_tok * rows for b in want)
+    for mode, call in ((1, single), (0, single), (1, None), (1, ragged), (2, ragged)):
+        got_flags, got = outcome(mode, call)
+        assert got_flags == flags
+        for g, b in zip(got, want):
+            assert np.array_equal(g, b)
+    ctx.destroy()
+
+
 def test_block_sizes(hc, torch):
     for B in (8, 32):
         rng = np.random.default_rng([5, B])
