@@ -1,5 +1,8 @@
 // RMSNorm instantiations of the restoration kernel, and the launch-shape selection shared by
 // all variants.
+#include <mutex>
+#include <set>
+
 #include "restore_kernel.inc"
 
 namespace hc {
@@ -10,14 +13,21 @@ hipError_t launch_mode0(const RestoreArgs& a, const TileGrid& g, unsigned grid, 
 }
 hipError_t configure_mode0() { return configure_mode<0>(); }
 
+// Function attributes are a device's, not a context's: set once per device (56 kernels, some 60 us).
 hipError_t configure_kernels() {
-  hipError_t e = configure_mode0();
+  static std::mutex mutex;
+  static std::set<int> done;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  e = configure_mode1();
-  if (e != hipSuccess) return e;
-  e = configure_mode2();
-  if (e != hipSuccess) return e;
-  return configure_mid();
+  std::lock_guard<std::mutex> lock(mutex);
+  if (done.count(dev)) return hipSuccess;
+  e = configure_mode0();
+  if (e == hipSuccess) e = configure_mode1();
+  if (e == hipSuccess) e = configure_mode2();
+  if (e == hipSuccess) e = configure_mid();
+  if (e == hipSuccess) done.insert(dev);
+  return e;
 }
 
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main) {

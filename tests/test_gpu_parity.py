@@ -537,6 +537,20 @@ def test_restore_context_from_store(hc, torch, pinned, loader, d_model):
     store.destroy()
 
 
+def test_restore_context_from_store_split(hc, torch, monkeypatch):
+    """The same with split launches asked for, so that every layer's launch is one whatever the launch rules
+    prefer."""
+    plain = hc.Context
+
+    def split_context(desc):
+        ctx = plain(desc)
+        ctx.set_split(2)
+        return ctx
+
+    monkeypatch.setattr(hc, "Context", split_context)
+    test_restore_context_from_store(hc, torch, True, 0, 2048)
+
+
 SEVERAL_LENGTHS = np.array([200, 0, 1, 333, 64], dtype=np.int32)
 SEVERAL_STORED = SEVERAL_LENGTHS + np.array([10, 5, 0, 0, 7])     # the store may hold more than is restored
 
