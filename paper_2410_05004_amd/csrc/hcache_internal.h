@@ -175,8 +175,9 @@ constexpr int kSmallMinModel = 1024;
 // Cost of a round of 256 workgroups (512 for nb = 1 beyond the first 256: two share a CU), from token
 // sweeps of d_model 256 .. 8192, 8 .. 56 heads: kMidStepUs per 64 channels and 3 + 0.7 nb for
 // prologue and epilogue; a round of the large tiles takes 1.5 and 5.  Launches of several layers run
-// their rounds into each other (fractions of a round count) and read every layer's weights from memory:
-// the hypotenuse with that time fits both kernels to 15 %, but for nb = 5, whose ring of two stages
+// their rounds into each other (fractions of a round count; with these tiles from four rounds on: 8 layers
+// of 4096 onto 2048, 560 tokens, 1.5 rounds of nb = 3 take 107 us, the large tiles 97) and read every
+// layer's weights from memory: the hypotenuse with that time fits both kernels to 15 %, but for nb = 5, whose ring of two stages
 // does not cover the memory's latency (300 tokens, 8 layers of 5120 onto 10240: 368 us against 308), and
 // which LayerNorm's extra matrix ops make slower than the large tiles (558 tokens of 7168 onto 14336:
 // 167 us against 153).  A single layer takes nb = 1 up to 512 workgroups only: beyond, the pairs lose step and
@@ -187,6 +188,10 @@ constexpr int kSmallMinModel = 1024;
 // tokens 111 / 126, 256 tokens 181 / 147 (not taken).
 constexpr float kMidStepUs[6] = {0.f, 0.40f, 0.58f, 0.77f, 0.98f, 1.20f};
 constexpr float kMidPairStepUs = 0.65f;                  // nb = 1, two workgroups on a CU
+// a round of large tiles that leaves every XCD some of its 32 CUs free (at most 20, 24 tiles on the busiest):
+// 4096 onto 8192 features, 1200 tokens 80 us; 7168 onto 14336, 558 tokens 151; against 1.5 per 64 channels
+// (below d_model 1024 prologue and epilogue hide the difference)
+constexpr float kWholeStepPart20Us = 1.2f, kWholeStepPart24Us = 1.3f;
 constexpr float kTileFixedUs = 5.f, kWeightsUsPerByte = 1.f / 5.4e6f;
 
 struct Route {
@@ -209,9 +214,14 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const float t = (kWholeStepUs * nm + kTileFixedUs) * (tiles > 1.f ? tiles : 1.f);
     best = sqrtf(t * t + all_weights_us * all_weights_us);
   } else {
-    best = (kWholeStepUs * nm + kTileFixedUs) * ceilf(tiles);
     SplitPlan sp;
     TileGrid g;
+    choose_tile_grid(nf, nt, g);
+    const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift);
+    const int supers = g.nsf * ((nt + gt - 1) / gt);
+    const int busiest = (supers + 7) / 8 * (gf < nf ? gf : nf) * (gt < nt ? gt : nt);   // tiles of the busiest XCD
+    const float step_us = nm < 16 ? kWholeStepUs : busiest <= 20 ? kWholeStepPart20Us : busiest <= 24 ? kWholeStepPart24Us : kWholeStepUs;
+    best = (step_us * nm + kTileFixedUs) * ceilf(tiles);
     if (free_order && plan_split(nf, nt, nm, false, sp, g)) {
       const int rest = n_tok - sp.nt_main * kTileT;      // tokens of the split tiles
       const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
@@ -227,7 +237,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const bool pair = b == 1 && wgs > 1.f;
     if (pair && n_layers == 1 && wgs > 2.f) continue;
     float rounds = pair ? wgs / 2 : wgs;
-    rounds = n_layers > 1 ? (rounds > 1.f ? rounds : 1.f) : ceilf(rounds);
+    if (n_layers == 1 || rounds < 4.f) rounds = ceilf(rounds);
     float t = 1.05f * rounds * ((pair ? kMidPairStepUs : kMidStepUs[b]) * nm + 3.f + 0.7f * b);
     if (n_layers > 1) t = sqrtf(t * t + all_weights_us * all_weights_us);
     if (t < best) { best = t; best_route = Route{Route::kMid, b}; }

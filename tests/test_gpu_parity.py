@@ -250,7 +250,7 @@ def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm):
     (64, 103, 64, 257, 1, 2, "bias"),      # three
     (192, 43, 128, 387, 1, 0, "layer"),    # four
     (512, 43, 128, 517, 1, 0, "rms"),      # five
-    (768, 43, 128, 77, 3, 0, "layer"),     # two token blocks per wave, several layers
+    (640, 43, 64, 75, 3, 0, "layer"),      # two token blocks per wave, several layers
     (64, 77, 64, 140, 3, 1, "rms"),        # three
     (192, 67, 64, 205, 3, 0, "bias"),      # four
 ])
