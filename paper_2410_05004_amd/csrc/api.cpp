@@ -115,7 +115,7 @@ static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, LayerBatch* bat
 hc_status restore_layer(hc_ctx* ctx, int32_t layer, const void* d_hidden,
                         const int32_t* d_positions, int32_t pos_base, int32_t n_tok,
                         const int32_t* d_cu, int32_t n_seq, const int32_t* d_tables,
-                        int32_t max_blocks, hipStream_t stream, bool allow_split) {
+                        int32_t max_blocks, hipStream_t stream) {
   const hc_layer_state& L = ctx->layers[layer];
   if (!L.wpack) return fail(HC_ESTATE, "hc_set_layer_weights was not called for this layer");
   if (!L.pool) return fail(HC_ESTATE, "hc_set_kv_pool was not called for this layer");
@@ -126,8 +126,7 @@ hc_status restore_layer(hc_ctx* ctx, int32_t layer, const void* d_hidden,
   a.mode = layer_mode(ctx, L);
   a.pool = L.pool;
   a.num_pages = L.num_pages;
-  a.split_ws = allow_split && ctx->split_mode ? ctx->split_ws : nullptr;
-  a.split_force = ctx->split_mode == 2;
+  set_split_rule(a, ctx->split_mode, ctx->split_ws, false);
   return timed_launch(ctx, a, nullptr, 1, stream);
 }
 
@@ -143,6 +142,7 @@ hc_status restore_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
     if (!aligned16(d_hidden[i])) return fail(HC_EALIGN, "hidden not 16-byte aligned");
   }
   RestoreArgs a = shared_args(ctx, d_positions, pos_base, n_tok, nullptr, 1, d_block_table, n_blocks);
+  set_split_rule(a, ctx->split_mode, ctx->split_ws, true);
   const int per_launch = layers_per_launch(2 * ctx->d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT);
   int i = 0;
   while (i < n_layers) {
@@ -490,6 +490,34 @@ hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
   out_plan[5] = split ? sp.n_split : 1;
   out_plan[6] = split ? sp.main_slots : 0;
   out_plan[7] = split ? sp.n_tail * kFixupPerTile : 0;
+  return HC_OK;
+}
+
+hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
+                        int32_t mode, int32_t* out_route) {
+  clear_error();
+  if (!out_route) return fail(HC_EINVAL, "null output pointer");
+  if (d_model <= 0 || d_model % 64 != 0 || d_kv <= 0 || d_kv % 64 != 0 || n_tok <= 0 || n_layers < 0)
+    return fail(HC_EINVAL, "bad shape");
+  if (norm_kind != HC_NORM_RMS && norm_kind != HC_NORM_LAYER) return fail(HC_EINVAL, "bad norm_kind");
+  if (mode < 0 || mode > 2) return fail(HC_EINVAL, "split mode must be 0, 1 or 2");
+  RestoreArgs a{};
+  a.n_tok = n_tok;
+  a.d_model = d_model;
+  a.d_kv = d_kv;
+  a.d_kv_pad = round_up(d_kv, kPartAlign);
+  a.mode = norm_kind == HC_NORM_LAYER ? 2 : 0;
+  float ws;                                              // stands for a context's workspace: not read
+  set_split_rule(a, mode, &ws, n_layers > 0);
+  const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT);
+  const int n = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
+  const Route route = restore_route(a, n);
+  SplitPlan sp;
+  TileGrid g;
+  out_route[0] = route.kind;
+  out_route[1] = route.nb;
+  out_route[2] = n_layers == 0 && restore_would_split(a, sp, g) ? sp.n_split : 1;
+  out_route[3] = n;
   return HC_OK;
 }
 

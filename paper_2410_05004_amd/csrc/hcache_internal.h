@@ -331,6 +331,11 @@ inline Route restore_route(const RestoreArgs& a, int n_layers) {
   if (a.split_force) return Route{Route::kTiles, 0};
   return plan_route(a.d_kv, a.d_model, a.n_tok, n_layers, a.mode == 2, a.split_ws != nullptr);
 }
+// What a context's split mode asks of a launch: `several` layers in one launch never split.
+inline void set_split_rule(RestoreArgs& a, int split_mode, float* split_ws, bool several) {
+  a.split_ws = !several && split_mode ? split_ws : nullptr;
+  a.split_force = !several && split_mode == 2;
+}
 // Whether a single-layer launch of `a` takes the split plan (a.split_ws set, routed to the tiles, and
 // plan_split agrees).
 bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main);
@@ -396,7 +401,7 @@ namespace hc {
 hc_status restore_layer(hc_ctx* ctx, int32_t layer, const void* d_hidden,
                         const int32_t* d_positions, int32_t pos_base, int32_t n_tok,
                         const int32_t* d_cu, int32_t n_seq, const int32_t* d_tables,
-                        int32_t max_blocks, hipStream_t stream, bool allow_split = true);
+                        int32_t max_blocks, hipStream_t stream);
 // The same for layers [layer_begin, layer_begin + n_layers) of one context, hidden states of
 // layer layer_begin + i at d_hidden[i] (host array of device pointers); as few launches as
 // kMaxLayersPerLaunch and equal kernel modes allow.

@@ -350,3 +350,27 @@ def test_split_plan_invariants(hc):
         hc.diag_split_plan(100, 64, 10)
     with pytest.raises(hc.HCacheError):
         hc.diag_split_plan(1024, 64, 10, 3)
+
+
+def test_route_invariants(hc):
+    """hc_diag_route (host logic only).  A context that asks for split launches gets the 256 x 256 tiles in
+    single-layer calls, split as the plan says; with splitting off no launch sums in another order (no split
+    tiles, no few-token kernel); several layers never split and never take the few-token kernel."""
+    for d_model in (64, 256, 1024, 4096, 8192):
+        for d_kv in (64, 192, 1024, 7168):
+            for n_tok in (1, 16, 65, 300, 1000, 2501, 16384):
+                for norm in (hc.HC_NORM_RMS, hc.HC_NORM_LAYER):
+                    for mode in (0, 1, 2):
+                        kernel, blocks, ways, layers = hc.diag_route(d_model, d_kv, n_tok, 0, norm, mode)
+                        plan = hc.diag_split_plan(d_model, d_kv, n_tok, mode)
+                        where = (d_model, d_kv, n_tok, norm, mode, kernel, blocks, ways)
+                        assert layers == 1 and ways == (plan["n_split"] if kernel == "tiles" else 1), where
+                        assert blocks in {"tiles": (0,), "few": (1, 2, 3, 4), "rows128": (1, 2, 3, 4, 5)}[kernel], where
+                        assert mode != 2 or kernel == "tiles", where
+                        assert kernel != "few" or (mode == 1 and d_model >= 1024), where
+                        for n_layers in (1, 3, 8, 40):
+                            kernel, blocks, ways, layers = hc.diag_route(d_model, d_kv, n_tok, n_layers, norm, mode)
+                            assert kernel != "few" and ways == 1 and min(n_layers, 8) <= layers <= min(n_layers, 32)
+    for bad in ((100, 64, 10), (1024, 60, 10), (1024, 64, 0), (1024, 64, 10, -1), (1024, 64, 10, 0, 2), (1024, 64, 10, 0, 0, 3)):
+        with pytest.raises(hc.HCacheError):
+            hc.diag_route(*bad)
