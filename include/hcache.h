@@ -391,8 +391,8 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * scatter).  Results are deterministic and within the same tolerance, but not bit-identical to
  * an unsplit launch (fp32 summation order).  Split launches of one context are ordered after
  * each other through an event, whatever their streams.  mode 0: never split.  mode 2: split
- * whenever the shape allows it (tests and measurements).  Launches over several layers
- * (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
+ * whenever the shape allows it (tests and measurements), and 256 x 256 tiles in every launch.
+ * Launches over several layers (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
  * a kernel of its own when that is faster than whole or split tiles (up to 500 tokens or so
  * with few heads, 50 with many); its workgroups' waves share the d_model loop, so the same holds
  * for its results; it uses no workspace and one launch.  In modes 0 and 1 launches that whole tiles

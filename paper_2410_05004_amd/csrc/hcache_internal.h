@@ -331,10 +331,11 @@ inline Route restore_route(const RestoreArgs& a, int n_layers) {
   if (a.split_force) return Route{Route::kTiles, 0};
   return plan_route(a.d_kv, a.d_model, a.n_tok, n_layers, a.mode == 2, a.split_ws != nullptr);
 }
-// What a context's split mode asks of a launch: `several` layers in one launch never split.
+// What a context's split mode asks of a launch: `several` layers in one launch never split, but they take
+// the 256 x 256 tiles too when split launches are asked for.
 inline void set_split_rule(RestoreArgs& a, int split_mode, float* split_ws, bool several) {
   a.split_ws = !several && split_mode ? split_ws : nullptr;
-  a.split_force = !several && split_mode == 2;
+  a.split_force = split_mode == 2;
 }
 // Whether a single-layer launch of `a` takes the split plan (a.split_ws set, routed to the tiles, and
 // plan_split agrees).

@@ -138,14 +138,17 @@ def test_opt30b_shape(hc):
     ctx.destroy()
 
 
-@pytest.mark.parametrize("norm_kind", [0, 1])
-def test_layers_in_one_launch(hc, norm_kind):
+@pytest.mark.parametrize("norm_kind,n_kv,per_launch,kernel_by_rule",
+                         [(0, 2, 32, "rows128"), (1, 2, 32, "rows128"), (1, 16, 16, "tiles")])
+def test_layers_in_one_launch(hc, norm_kind, n_kv, per_launch, kernel_by_rule):
     """hc_restore_kv_layers over 35 layers (more than one launch holds; layers with and without
     a bias, so the kernel mode changes along the way) writes bit for bit what one
-    hc_restore_kv per layer writes, and that is the oracle's result."""
+    hc_restore_kv per layer writes, and that is the oracle's result; on the kernel that the launch rule
+    takes, and on the 256 x 256 tiles, whose second token tile is ragged, that a context gets which asks
+    for split launches."""
     import torch
-    rng = np.random.default_rng([9, norm_kind])
-    L, d_model, n_kv, hd, B, T = 35, 256, 2, 64, 16, 300
+    rng = np.random.default_rng([9, norm_kind] if n_kv == 2 else [9, norm_kind, n_kv])
+    L, d_model, hd, B, T = 35, 256, 64, 16, 300
     d_kv = n_kv * hd
     n_blocks = 24
     num_pages = n_blocks + 4
@@ -176,17 +179,24 @@ def test_layers_in_one_launch(hc, norm_kind):
     for l in range(L):
         ctx.set_kv_pool(l, pools_a[l], num_pages)
         ctx.restore_kv(l, hidden[l], d_pos, T, d_bt, n_blocks, s)
-    for l in range(L):
-        ctx.set_kv_pool(l, pools_b[l], num_pages)
-    ctx.timing_begin()
-    ctx.restore_kv_layers(0, hidden, d_pos, T, d_bt, n_blocks, s)
-    _, launches = ctx.timing_end(s)
-    assert ctx.poll_device_error(s) == 0
-    # two tiles per layer: up to 32 layers go into one launch (short contexts fill the chip with layers)
-    if norm_kind == 1:
-        assert launches == 2                              # one mode: 32 + 3 layers
-    else:
-        assert launches > 2                               # the mode changes with the bias
+    # two or sixteen tiles per layer: so many layers go into one launch (short contexts fill the chip with layers)
+    for mode, kernel in ((2, "tiles"), (1, kernel_by_rule)):
+        assert hc.diag_route(d_model, d_kv, T, L, norm_kind, mode)[::3] == (kernel, per_launch)
+        ctx.set_split(mode)
+        for l in range(L):
+            pools_b[l] = gh.new_pool(num_pages, B, n_kv, hd)
+            ctx.set_kv_pool(l, pools_b[l], num_pages)
+        ctx.timing_begin()
+        ctx.restore_kv_layers(0, hidden, d_pos, T, d_bt, n_blocks, s)
+        _, launches = ctx.timing_end(s)
+        assert ctx.poll_device_error(s) == 0
+        if norm_kind == 1:
+            assert launches == -(-L // per_launch)        # one mode: 32 + 3 or 16 + 16 + 3 layers
+        else:
+            assert launches > 2                           # the mode changes with the bias
+        for l in range(L):
+            assert torch.equal(pools_a[l].view(torch.int16), pools_b[l].view(torch.int16)), \
+                f"layer {l}, {kernel}: fused launch differs from the single-layer launch"
     for l in (0, 1, 2, 3, 17, 31, 32, 34):
         a, b = gh.pool_bits(pools_a[l]), gh.pool_bits(pools_b[l])
         assert np.array_equal(a, b), f"layer {l}: fused launch differs from the single-layer launch"

@@ -354,7 +354,7 @@ def test_split_plan_invariants(hc):
 
 def test_route_invariants(hc):
     """hc_diag_route (host logic only).  A context that asks for split launches gets the 256 x 256 tiles in
-    single-layer calls, split as the plan says; with splitting off no launch sums in another order (no split
+    every call, split as the plan says in single-layer ones; with splitting off no launch sums in another order (no split
     tiles, no few-token kernel); several layers never split and never take the few-token kernel."""
     for d_model in (64, 256, 1024, 4096, 8192):
         for d_kv in (64, 192, 1024, 7168):
@@ -371,6 +371,7 @@ def test_route_invariants(hc):
                         for n_layers in (1, 3, 8, 40):
                             kernel, blocks, ways, layers = hc.diag_route(d_model, d_kv, n_tok, n_layers, norm, mode)
                             assert kernel != "few" and ways == 1 and min(n_layers, 8) <= layers <= min(n_layers, 32)
+                            assert mode != 2 or kernel == "tiles", (d_model, d_kv, n_tok, n_layers, norm)
     for bad in ((100, 64, 10), (1024, 60, 10), (1024, 64, 0), (1024, 64, 10, -1), (1024, 64, 10, 0, 2), (1024, 64, 10, 0, 0, 3)):
         with pytest.raises(hc.HCacheError):
             hc.diag_route(*bad)
