@@ -97,13 +97,11 @@ static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, LayerBatch* bat
     }
     HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used], stream));
   }
-  SplitPlan sp;
-  TileGrid g_main;
-  const bool split = !batch && restore_would_split(a, sp, g_main);
+  const Route route = restore_route(a, n_layers);
   // the workspace is one per context: a split launch waits for the one before it, whatever its stream
-  if (split) HC_HIP(hipStreamWaitEvent(stream, ctx->split_done, 0));
-  HC_HIP(launch_restore(a, batch, n_layers, stream));
-  if (split) HC_HIP(hipEventRecord(ctx->split_done, stream));
+  if (route.split) HC_HIP(hipStreamWaitEvent(stream, ctx->split_done, 0));
+  HC_HIP(launch_restore(a, route, batch, n_layers, stream));
+  if (route.split) HC_HIP(hipEventRecord(ctx->split_done, stream));
   if (timed) {
     HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used + 1], stream));
     ctx->ev_used += 2;
@@ -512,11 +510,9 @@ hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_
   const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT);
   const int n = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
   const Route route = restore_route(a, n);
-  SplitPlan sp;
-  TileGrid g;
   out_route[0] = route.kind;
   out_route[1] = route.nb;
-  out_route[2] = n_layers == 0 && restore_would_split(a, sp, g) ? sp.n_split : 1;
+  out_route[2] = route.split ? route.split_plan.n_split : 1;
   out_route[3] = n;
   return HC_OK;
 }

@@ -195,16 +195,19 @@ constexpr float kWholeStepPart20Us = 1.2f, kWholeStepPart24Us = 1.3f;
 constexpr float kTileFixedUs = 5.f, kWeightsUsPerByte = 1.f / 5.4e6f;
 
 struct Route {
-  enum Kind { kTiles, kSmall, kMid } kind;
-  int nb;
+  enum Kind { kTiles, kSmall, kMid } kind = kTiles;
+  int nb = 0;              // token blocks per workgroup of the other two
+  bool split = false;      // kTiles: the launch is split by
+  SplitPlan split_plan{};
+  TileGrid grid{};         // kTiles: of the tiles computed whole
 };
-// Which kernel a launch of n_layers layers takes.  `free_order`: the order of the sums may depend on the
-// token count (split launches allowed); the few-token kernel and split plans need it.
+// Which kernel a launch of n_layers layers takes, decided once per launch.  `free_order`: the order of the
+// sums may depend on the token count (split launches allowed); the few-token kernel and split plans need it.
 inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool layer_norm, bool free_order) {
   const int nm = d_model / (2 * kTileK);
   const float weights_us = 4.f * d_kv * d_model * kWeightsUsPerByte;
   const float all_weights_us = weights_us * n_layers;
-  Route best_route{Route::kTiles, 0};
+  Route route;
 
   // the 256 x 256 tiles, whole or split
   const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF, nt = (n_tok + kTileT - 1) / kTileT;
@@ -214,15 +217,16 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const float t = (kWholeStepUs * nm + kTileFixedUs) * (tiles > 1.f ? tiles : 1.f);
     best = sqrtf(t * t + all_weights_us * all_weights_us);
   } else {
-    SplitPlan sp;
-    TileGrid g;
+    SplitPlan& sp = route.split_plan;
+    TileGrid& g = route.grid;
     choose_tile_grid(nf, nt, g);
     const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift);
     const int supers = g.nsf * ((nt + gt - 1) / gt);
     const int busiest = (supers + 7) / 8 * (gf < nf ? gf : nf) * (gt < nt ? gt : nt);   // tiles of the busiest XCD
     const float step_us = nm < 16 ? kWholeStepUs : busiest <= 20 ? kWholeStepPart20Us : busiest <= 24 ? kWholeStepPart24Us : kWholeStepUs;
     best = (step_us * nm + kTileFixedUs) * ceilf(tiles);
-    if (free_order && plan_split(nf, nt, nm, false, sp, g)) {
+    route.split = free_order && plan_split(nf, nt, nm, false, sp, g);
+    if (route.split) {
       const int rest = n_tok - sp.nt_main * kTileT;      // tokens of the split tiles
       const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
       float loop = 1.1f * kSplitStepUs * nm / sp.n_split;   // with most CUs busy
@@ -240,7 +244,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     if (n_layers == 1 || rounds < 4.f) rounds = ceilf(rounds);
     float t = 1.05f * rounds * ((pair ? kMidPairStepUs : kMidStepUs[b]) * nm + 3.f + 0.7f * b);
     if (n_layers > 1) t = sqrtf(t * t + all_weights_us * all_weights_us);
-    if (t < best) { best = t; best_route = Route{Route::kMid, b}; }
+    if (t < best) { best = t; route.kind = Route::kMid; route.nb = b; }
   }
 
   if (n_layers == 1 && free_order && d_model >= kSmallMinModel) {
@@ -255,9 +259,10 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     }
     const float stream_us = 2.85e-5f * d_model * cost;
     const float t = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
-    if (t < best) { best = t; best_route = Route{Route::kSmall, nb}; }
+    if (t < best) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
-  return best_route;
+  if (route.kind != Route::kTiles) route.split = false;
+  return route;
 }
 
 // Arguments of one restoration launch (device pointers unless noted).
@@ -320,16 +325,21 @@ struct LayerBatch {
 };
 
 // Launchers implemented in the .hip files.  All are asynchronous on `stream`.
-// `batch` null: one layer from `a`; else n_layers <= kMaxLayersPerLaunch layers in one launch.
-hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream);
+// `batch` null: one layer from `a`; else n_layers <= kMaxLayersPerLaunch layers in one launch.  `route` is
+// restore_route's for the same arguments.
+hipError_t launch_restore(const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers, hipStream_t stream);
 // Tiles of 128 packed rows x 64 nb tokens (nb 1..5), one launch; `batch` as in launch_restore.
 hipError_t launch_restore_mid(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
 hipError_t launch_restore_small(const RestoreArgs& a, int nb, hipStream_t stream);
 // The kernel a launch of n_layers layers of `a` takes.  A context that asks for split launches gets the
 // 256 x 256 tiles.
 inline Route restore_route(const RestoreArgs& a, int n_layers) {
-  if (a.split_force) return Route{Route::kTiles, 0};
-  return plan_route(a.d_kv, a.d_model, a.n_tok, n_layers, a.mode == 2, a.split_ws != nullptr);
+  Route r;
+  if (!a.split_force) r = plan_route(a.d_kv, a.d_model, a.n_tok, n_layers, a.mode == 2, a.split_ws != nullptr);
+  else if (a.split_ws)
+    r.split = plan_split(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, a.d_model / (2 * kTileK), true, r.split_plan, r.grid);
+  r.split_plan.ws = a.split_ws;
+  return r;
 }
 // What a context's split mode asks of a launch: `several` layers in one launch never split, but they take
 // the 256 x 256 tiles too when split launches are asked for.
@@ -337,9 +347,6 @@ inline void set_split_rule(RestoreArgs& a, int split_mode, float* split_ws, bool
   a.split_ws = !several && split_mode ? split_ws : nullptr;
   a.split_force = split_mode == 2;
 }
-// Whether a single-layer launch of `a` takes the split plan (a.split_ws set, routed to the tiles, and
-// plan_split agrees).
-bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main);
 hipError_t launch_pack_weights(const uint16_t* wkv, const uint16_t* gamma, uint16_t* wpack,
                                int d_model, int d_kv, int head_dim, int rope_style,
                                hipStream_t stream);

@@ -30,24 +30,13 @@ hipError_t configure_kernels() {
   return e;
 }
 
-bool restore_would_split(const RestoreArgs& a, SplitPlan& sp, TileGrid& g_main) {
-  if (!a.split_ws || a.n_tok <= 0 || restore_route(a, 1).kind != Route::kTiles) return false;
-  return plan_split(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, a.d_model / (2 * kTileK), a.split_force != 0, sp, g_main);
-}
-
-hipError_t launch_restore(const RestoreArgs& a, LayerBatch* batch, int n_layers, hipStream_t stream) {
-  if (a.n_tok <= 0) return hipSuccess;
-  const Route route = restore_route(a, batch ? n_layers : 1);
+hipError_t launch_restore(const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers, hipStream_t stream) {
   if (route.kind == Route::kMid) return launch_restore_mid(a, route.nb, batch, n_layers, stream);
-  if (!batch && route.kind == Route::kSmall) return launch_restore_small(a, route.nb, stream);
-  TileGrid g;
-  SplitPlan sp;
-  const SplitPlan* use_split = nullptr;
+  if (route.kind == Route::kSmall) return launch_restore_small(a, route.nb, stream);
+  TileGrid g = route.grid;
+  const SplitPlan* use_split = route.split ? &route.split_plan : nullptr;
   unsigned grid = 0;
-  if (!batch && restore_would_split(a, sp, g)) {
-    sp.ws = a.split_ws;
-    use_split = &sp;
-  } else {
+  if (!use_split) {
     grid = (unsigned)choose_tile_grid(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, g);
     if (batch) {
       batch->slots_per_layer = (int32_t)grid;
