@@ -158,16 +158,22 @@ __host__ __device__ inline void split_range(int nm, int n, int s, int& m_begin, 
 //
 // A launch is as long as the busiest CU takes to stream its operands: 64 bytes per channel for the
 // rows and 32 nb for the tokens, per workgroup; up to nb = 2 two workgroups share a CU, so
-// their load evens out.  Token sweeps (d_model 1024 .. 8192, 8 .. 56 heads, 5 .. 512 tokens) fit
-// 3.5 us + the hypotenuse of that (2.85e-5 us per channel and unit of 32 + 16 nb) and the time
+// their load evens out.  The 64-row pair groups go round the XCDs and all token tiles of a group stay on
+// its XCD, so the busiest CU is one of an XCD with ceil(pair groups / 8) of them (128 features are two
+// pair groups, on two of the eight XCDs).
+// Token sweeps (d_model 1024 .. 8192, 1 .. 56 heads, 1 .. 9000 tokens) fit
+// 3.5 us + the hypotenuse of that (2.85e-5 us per channel and unit of 32 + 16 nb, and 3 us more for the
+// lookups and the reduction of every further round of workgroups) and the time
 // the weights take from memory (5.4 MB/us), to 20 %.  The other side of the comparison is what
 // plan_split's figures give for the tiles, with the workspace traffic of the live token blocks only.
 // Below d_model 1024 the large tiles' workgroups take too short for a second order of sums to
 // be worth having: there every launch adds a token's channels up in the same order.
 // Measured, this kernel against the tiles: 16 tokens 10.2 / 24.8 us (d_model 4096, 8 heads),
 // 18.7 / 34.5 (32 heads), 29.3 / 41.7 (5120, 40 heads); 64 tokens 10.4 / 26.6, 23.6 / 36.6, 40.6 /
-// 43.9; 256 tokens 15.9 / 34.1, 61.3 / 47.7, 88.0 / 59.5.
+// 43.9; 256 tokens 15.9 / 34.1, 61.3 / 47.7, 88.0 / 59.5.  Narrow K/V: 1700 tokens of 4096 channels
+// onto 128 features 24.4 / 32.8, 4000 tokens 47.8 / 39.8 (not taken), 9000 of 1024 channels 53.7 / 26.4 (not taken).
 constexpr int kSmallMinModel = 1024;
+constexpr float kSmallRoundUs = 3.f;
 
 // Tiles of 128 rows x 64 nb tokens (restore_mid.inc).  They add a token's channels up in the order of the
 // unsplit 256 x 256 tiles, so results do not depend on which of the two a launch takes.
@@ -248,16 +254,16 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
   }
 
   if (n_layers == 1 && free_order && d_model >= kSmallMinModel) {
-    const int units = 2 * d_kv / 32;
+    const int units = (2 * d_kv / kPairGroup + 7) / 8 * 2;   // 32-row units of the busiest XCD
     int nb = 0;
-    float cost = 0.f;
+    float stream_us = 0.f;
     for (int b = 1; b <= 4; ++b) {
-      const float wgs = (float)units * ((n_tok + 16 * b - 1) / (16 * b)) / kChipCUs;
-      const float rounds = b <= 2 ? (wgs > 1.f ? wgs : 1.f) : ceilf(wgs);
-      const float c = rounds * (32 + 16 * b);
-      if (b == 1 || c < cost) { cost = c; nb = b; }
+      const float load = (float)units * ((n_tok + 16 * b - 1) / (16 * b)) / (kChipCUs / 8);   // workgroups per CU
+      const float in_turn = b <= 2 ? (load > 1.f ? load : 1.f) : ceilf(load);
+      const float rounds = b <= 2 ? (load > 2.f ? load / 2 : 1.f) : in_turn;
+      const float t = 2.85e-5f * d_model * in_turn * (32 + 16 * b) + kSmallRoundUs * (rounds - 1.f);
+      if (b == 1 || t < stream_us) { stream_us = t; nb = b; }
     }
-    const float stream_us = 2.85e-5f * d_model * cost;
     const float t = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
     if (t < best) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }

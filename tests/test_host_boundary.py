@@ -375,3 +375,22 @@ def test_route_invariants(hc):
     for bad in ((100, 64, 10), (1024, 60, 10), (1024, 64, 0), (1024, 64, 10, -1), (1024, 64, 10, 0, 2), (1024, 64, 10, 0, 0, 3)):
         with pytest.raises(hc.HCacheError):
             hc.diag_route(*bad)
+
+
+# Measured on MI355X: (d_model, d_kv, tokens, us of the few-token kernel, us of the 256 x 256 tiles, whole or split)
+FEW_TOKEN_TIMES = [
+    (1024, 64, 400, 5.2, 26.4), (1024, 64, 6000, 36.5, 25.7), (1024, 64, 9000, 53.7, 26.4), (2048, 64, 1700, 15.2, 29.9),
+    (2048, 64, 6000, 51.2, 34.9), (4096, 64, 2600, 38.5, 36.2), (4096, 64, 4000, 47.8, 39.8), (4096, 64, 6000, 76.0, 42.7),
+    (4096, 128, 2600, 41.2, 37.2), (4096, 128, 4000, 51.1, 41.0), (8192, 128, 700, 25.2, 39.0), (8192, 128, 2600, 68.0, 46.9),
+    (8192, 128, 4000, 96.4, 50.8), (4096, 1024, 40, 9.9, 26.8), (4096, 1024, 128, 12.1, 29.6), (8192, 1024, 40, 16.3, 30.6),
+]
+
+
+def test_few_token_kernel_only_where_it_was_measured_faster(hc):
+    """The launch rule against measured times, narrow K/V parts and long contexts included (few row groups lie on few
+    of the XCDs): a layer never goes to the few-token kernel where that took longer than the large tiles."""
+    for d_model, d_kv, n_tok, few_us, tiles_us in FEW_TOKEN_TIMES:
+        kernel = hc.diag_route(d_model, d_kv, n_tok)[0]
+        assert kernel != "few" or few_us < tiles_us, (d_model, d_kv, n_tok, few_us, tiles_us)
+    for d_model, d_kv, n_tok in ((4096, 1024, 40), (4096, 1024, 128), (8192, 1024, 40), (2048, 64, 400)):
+        assert hc.diag_route(d_model, d_kv, n_tok)[0] == "few"
