@@ -147,8 +147,8 @@ hc_status hc_restore_kv(hc_ctx* ctx, int32_t layer, const void* d_hidden,
  * are ALL resident in HBM: h_d_hidden is a HOST array of n_layers device pointers, entry i =
  * bf16 [n_tok, d_model] of layer layer_begin + i; positions and block table are shared (one
  * context).  The layers go out in launches of up to 8 layers each (for short contexts, whose
- * layers have fewer than 32 tiles of 256 features x 256 tokens: as many layers as fill the 256
- * compute units once, up to 32), which removes the gaps between per-layer kernels and lets the
+ * layers have fewer than 32 tiles of 256 features x 256 tokens: up to as many layers as fill the 256
+ * compute units once, at most 32), which removes the gaps between per-layer kernels and lets the
  * compute units run out of step.
  * Per layer the result is identical to hc_restore_kv's.  Every layer needs weights and a
  * pool (HC_ESTATE).  The pointer array is read during the call only. */

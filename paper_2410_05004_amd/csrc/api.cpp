@@ -141,7 +141,7 @@ hc_status restore_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
   }
   RestoreArgs a = shared_args(ctx, d_positions, pos_base, n_tok, nullptr, 1, d_block_table, n_blocks);
   set_split_rule(a, ctx->split_mode, ctx->split_ws, true);
-  const int per_launch = layers_per_launch(2 * ctx->d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT);
+  const int per_launch = layers_per_launch(2 * ctx->d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT, n_layers);
   int i = 0;
   while (i < n_layers) {
     // one launch per run of layers with the same kernel mode, at most per_launch of them
@@ -507,7 +507,7 @@ hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_
   a.mode = norm_kind == HC_NORM_LAYER ? 2 : 0;
   float ws;                                              // stands for a context's workspace: not read
   set_split_rule(a, mode, &ws, n_layers > 0);
-  const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT);
+  const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT, n_layers);
   const int n = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
   const Route route = restore_route(a, n);
   out_route[0] = route.kind;

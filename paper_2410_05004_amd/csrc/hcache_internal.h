@@ -90,6 +90,41 @@ inline int choose_tile_grid(int nf, int nt, TileGrid& g) {
   return best_slots * 8;
 }
 
+// How the workgroups of a launch spread over the chip's 32 shader engines (four per XCD, eight CUs each).
+// The ids of an XCD go round its engines in order, those that exit at once included, so an engine can have
+// more than eight workgroups while others have CUs free, and the launch then takes another round:
+// 3 layers of 1088 channels onto 1152 features, 714 tokens in tiles of 128 rows x 256, are 30 workgroups on the busiest XCD
+// but 9 on one of its engines, and took 35.7 us instead of the 22 of one round.  Over 2000 measured launches of
+// several layers, those of up to 32 workgroups on an XCD but more than 8 on an engine took 1.6 times
+// the one round's time, the others 0.9.
+struct ChipLoad {
+  int part[9][32];         // workgroups of each engine in the first m layers, m = 0 .. 8
+
+  // `slots` of a layer as choose_tile_grid returns them; tiles from feature tile `live_nf` on exit at once
+  ChipLoad(const TileGrid& g, int slots, int live_nf) : part{} {
+    const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift), per_xcd = slots >> 3;
+    const int n_super = g.nsf * ((g.nt + gt - 1) / gt);
+    int own[8][4] = {};                                    // one layer's, by super tile column and engine
+    for (int k = 0; k < n_super; ++k) {
+      const int f0 = k % g.nsf * gf, t0 = k / g.nsf * gt, at = (k >> 3) << g.g_shift;
+      for (int t = 0; t < gt && t0 + t < g.nt; ++t)
+        for (int f = 0; f < gf && f0 + f < live_nf; ++f) ++own[k & 7][(at + f + t * gf) & 3];
+    }
+    for (int m = 0; m < 8; ++m)                            // layer m: its super tile k on XCD (k - m) % 8
+      for (int e = 0; e < 32; ++e)
+        part[m + 1][e] = part[m][e] + own[((e >> 2) + m) & 7][(e - m * per_xcd) & 3];
+  }
+  // rounds of a launch of n layers, `per_cu` workgroups on a CU at a time
+  int rounds(int n, int per_cu = 1) const {
+    int most = 0;
+    for (int e = 0; e < 32; ++e) {
+      const int here = n / 8 * part[8][e] + part[n % 8][e];
+      if (here > most) most = here;
+    }
+    return (most + 8 * per_cu - 1) / (8 * per_cu);
+  }
+};
+
 // Split d_model loops for a partly filled last round (paper Section 4.1.1, "Performance
 // considerations": the projection's efficiency depends on how the token count fills the device).
 // A single-layer launch of nf x nt tiles runs in rounds of one workgroup per CU, and a last
@@ -315,15 +350,29 @@ struct LayerEntry {
 // workgroups to hide the gaps between kernels, few enough that the CUs of an XCD stay close
 // together and keep sharing weights in its L2 (measured at 256 tiles per layer: 16 and 32
 // layers per launch fetch 4 % and 37 % more, and are no faster).  When a layer has fewer than
-// 32 tiles (a short context), as many layers as fill one round of 256 workgroups, up to 32:
-// a launch takes a round's time however few of the CUs it uses.  Such a layer's tiles are one
-// super tile and lie on one XCD, consecutive layers on consecutive XCDs, so the count is a
-// multiple of 8: with ten layers of 24 tiles two XCDs would run two of them, one after the other
-// (32 layers of 4096 onto 2048, 600 tokens: 578 us with ten layers a launch, 381 with eight).
+// 32 tiles (a short context), up to as many layers as would fill one round of 256 workgroups, at most 32:
+// a launch takes a round's time however few of the CUs it uses.  Such a layer's tiles lie on few XCDs,
+// consecutive layers on consecutive ones, so a launch can take two rounds with CUs free elsewhere; the count
+// is the one with the fewest rounds over all launches of the call, and of those with the fewest launches.
+// 32 layers of 4096 onto 2048, 600 tokens (24 tiles a layer): 578 us in tens, which take two rounds each
+// but for the last two layers, 381 in eights, which take one; 10 layers of 640 onto 5632, 239 tokens (22
+// tiles): 36.8 us in one launch of two rounds, 56.8 as 8 + 2; 20 of 128 onto 1536, 271 tokens: 27.1 in
+// one launch, 36.2 as 16 + 4.
 constexpr int kMaxLayersPerLaunch = 32;
-inline int layers_per_launch(int nf, int nt) {
-  const int by_round = kChipCUs / (nf * nt) & ~7;
-  return by_round < 8 ? 8 : by_round > kMaxLayersPerLaunch ? kMaxLayersPerLaunch : by_round;
+inline int layers_per_launch(int nf, int nt, int n_layers) {
+  int most = kChipCUs / (nf * nt);
+  if (most > kMaxLayersPerLaunch) most = kMaxLayersPerLaunch;
+  if (most > n_layers) most = n_layers;
+  if (most <= 8) return 8;
+  TileGrid g;
+  const int slots = choose_tile_grid(nf, nt, g);
+  const ChipLoad load(g, slots, nf);
+  int best = 0, best_rounds = 0;
+  for (int n = most; n >= 8; --n) {
+    const int rounds = n_layers / n * load.rounds(n) + load.rounds(n_layers % n);
+    if (best == 0 || rounds < best_rounds) { best = n; best_rounds = rounds; }
+  }
+  return best;
 }
 struct LayerBatch {
   LayerEntry e[kMaxLayersPerLaunch];

@@ -394,3 +394,70 @@ def test_few_token_kernel_only_where_it_was_measured_faster(hc):
         assert kernel != "few" or few_us < tiles_us, (d_model, d_kv, n_tok, few_us, tiles_us)
     for d_model, d_kv, n_tok in ((4096, 1024, 40), (4096, 1024, 128), (8192, 1024, 40), (2048, 64, 400)):
         assert hc.diag_route(d_model, d_kv, n_tok)[0] == "few"
+
+
+# Measured on MI355X: (d_model, d_kv, tokens, layers, {layers in the first launch: us of the call}), 256 x 256 tiles
+LAYERS_PER_LAUNCH_TIMES = [
+    (640, 2816, 239, 10, {8: 56.8, 10: 36.8}), (256, 2688, 173, 10, {8: 32.0, 10: 23.5}),
+    (256, 3456, 72, 9, {8: 30.3, 9: 22.3}), (128, 768, 271, 20, {16: 36.2, 20: 27.1}),
+    (1344, 256, 2179, 10, {8: 132.5, 10: 101.0}), (5056, 2496, 1, 9, {8: 205.6, 9: 100.5}),
+    (4672, 3008, 32, 9, {8: 203.5, 9: 111.4}), (1152, 1152, 529, 9, {8: 92.6, 9: 71.8}),
+    (4096, 1024, 600, 32, {8: 381.0, 10: 578.0}),
+]
+
+
+def test_layers_per_launch_against_measured_times(hc):
+    """How many layers of a short context go into a launch: the count that was measured fastest."""
+    for d_model, d_kv, n_tok, n_layers, us in LAYERS_PER_LAUNCH_TIMES:
+        n = hc.diag_route(d_model, d_kv, n_tok, n_layers, mode=2)[3]
+        assert n in us and us[n] == min(us.values()), (d_model, d_kv, n_tok, n_layers, n, us)
+    # 256 tiles or more a layer: eight; never more than 32; a call of at most eight layers is one launch
+    assert hc.diag_route(4096, 1024, 8192, 32)[3] == 8 and hc.diag_route(256, 128, 20, 100)[3] <= 32
+    assert hc.diag_route(4096, 1024, 600, 8)[3] == 8
+
+
+def test_chip_load_matches_the_tile_map(hc, tmp_path):
+    """ChipLoad (the closed form the launch rules use) against a count over the tile map, which the kernels
+    compile: the workgroup of slot w of layer l runs on XCD (l slots + w) % 8, and the ids of an XCD go round its four
+    engines."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src = tmp_path / "load.cpp"
+    src.write_text("""
+#include <cstdio>
+#include "hcache_internal.h"
+using namespace hc;
+int main() {
+  int bad = 0, n = 0;
+  for (int nf : {1, 2, 3, 5, 8, 9, 10, 18, 40, 80, 112})
+    for (int nt : {1, 2, 3, 5, 7, 16, 33})
+      for (int live = nf > 1 ? nf - 1 : 1; live <= nf; ++live) {
+        TileGrid g;
+        const int slots = choose_tile_grid(nf, nt, g);
+        const ChipLoad load(g, slots, live);
+        int count[32] = {};
+        for (int l = 0; l < 33; ++l) {
+          for (int per_cu = 1; per_cu <= 2; ++per_cu) {
+            int most = 0;
+            for (int c : count) most = c > most ? c : most;
+            bad += load.rounds(l, per_cu) != (most + 8 * per_cu - 1) / (8 * per_cu);
+            ++n;
+          }
+          for (int w = 0; w < slots; ++w) {
+            int f, t;
+            const int id = l * slots + w;
+            if (slot_to_tile(g, w, l, f, t) && f < live) ++count[(id & 7) * 4 + (id >> 3 & 3)];
+          }
+        }
+      }
+  std::printf("%d of %d differ\\n", bad, n);
+  return bad != 0;
+}
+""")
+    inc = [os.path.join(ROOT, "include"), os.path.join(ROOT, "paper_2410_05004_amd", "csrc")]
+    exe = tmp_path / "load"
+    subprocess.run([hipcc, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-I", inc[0], "-I", inc[1],
+                    str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
