@@ -75,7 +75,7 @@ inline int choose_tile_grid(int nf, int nt, TileGrid& g) {
   for (int fs = 0; fs <= 5; ++fs) {
     for (int ts = 0; fs + ts <= 5; ++ts) {
       const int gf = 1 << fs, gt = 1 << ts;
-      const int n_super = ((nf + gf - 1) / gf) * ((nt + gt - 1) / gt);
+      const int n_super = ((nf + gf - 1) >> fs) * ((nt + gt - 1) >> ts);
       const int slots = (n_super + 7) / 8 * gf * gt;      // workgroup slots per XCD
       const int rounds = (slots + 31) / 32;
       const int share = (32 >> fs) + (32 >> ts);          // 32 * (1/GF + 1/GT)
@@ -98,32 +98,70 @@ inline int choose_tile_grid(int nf, int nt, TileGrid& g) {
 // several layers, those of up to 32 workgroups on an XCD but more than 8 on an engine took 1.6 times
 // the one round's time, the others 0.9.
 struct ChipLoad {
-  int part[9][32];         // workgroups of each engine in the first m layers, m = 0 .. 8
+  int part[9][32];         // workgroups of each engine (4 x XCD + engine) in the first m layers, m = 0 .. 8
 
   // `slots` of a layer as choose_tile_grid returns them; tiles from feature tile `live_nf` on exit at once
   ChipLoad(const TileGrid& g, int slots, int live_nf) : part{} {
     const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift), per_xcd = slots >> 3;
-    const int n_super = g.nsf * ((g.nt + gt - 1) / gt);
-    int own[8][4] = {};                                    // one layer's, by super tile column and engine
-    for (int k = 0; k < n_super; ++k) {
-      const int f0 = k % g.nsf * gf, t0 = k / g.nsf * gt, at = (k >> 3) << g.g_shift;
-      for (int t = 0; t < gt && t0 + t < g.nt; ++t)
-        for (int f = 0; f < gf && f0 + f < live_nf; ++f) ++own[k & 7][(at + f + t * gf) & 3];
+    int own[8][4] = {};                                    // one layer's, by super tile k % 8 and engine
+    for (int t0 = 0, k = 0; t0 < g.nt; t0 += gt)
+      for (int i = 0; i < g.nsf; ++i, ++k) {
+        const int nf_here = live_nf - i * gf < gf ? live_nf - i * gf : gf, nt_here = g.nt - t0 < gt ? g.nt - t0 : gt;
+        const int at = (k >> 3) << g.g_shift;
+        if (gf >= 4)                                       // tile f of every row is on engine f % 4
+          for (int e = 0; e < 4; ++e) own[k & 7][e] += nf_here > e ? (nf_here - e + 3) / 4 * nt_here : 0;
+        else
+          for (int t = 0; t < nt_here; ++t)
+            for (int f = 0; f < nf_here; ++f) ++own[k & 7][(at + f + t * gf) & 3];
+      }
+    for (int m = 0; m < 8; ++m) {                          // layer m: its super tile k on XCD (k - m) % 8
+      const int turn = m * per_xcd & 3;                    // and its first slot on engine `turn`
+      for (int x = 0; x < 8; ++x) {
+        const int* here = own[(x + m) & 7];
+        if (turn == 0)
+          for (int e = 0; e < 4; ++e) part[m + 1][4 * x + e] = part[m][4 * x + e] + here[e];
+        else
+          for (int e = 0; e < 4; ++e) part[m + 1][4 * x + e] = part[m][4 * x + e] + here[(e - turn) & 3];
+      }
     }
-    for (int m = 0; m < 8; ++m)                            // layer m: its super tile k on XCD (k - m) % 8
-      for (int e = 0; e < 32; ++e)
-        part[m + 1][e] = part[m][e] + own[((e >> 2) + m) & 7][(e - m * per_xcd) & 3];
   }
-  // rounds of a launch of n layers, `per_cu` workgroups on a CU at a time
-  int rounds(int n, int per_cu = 1) const {
+  // workgroups on the busiest engine, and XCD, in a launch of n layers; its rounds at eight an engine at a time
+  int busiest(int n) const {
     int most = 0;
     for (int e = 0; e < 32; ++e) {
       const int here = n / 8 * part[8][e] + part[n % 8][e];
       if (here > most) most = here;
     }
-    return (most + 8 * per_cu - 1) / (8 * per_cu);
+    return most;
   }
+  int busiest_xcd(int n) const {
+    int most = 0;
+    for (int x = 0; x < 32; x += 4) {
+      int here = 0;
+      for (int e = x; e < x + 4; ++e) here += n / 8 * part[8][e] + part[n % 8][e];
+      if (here > most) most = here;
+    }
+    return most;
+  }
+  int rounds(int n) const { return (busiest(n) + 7) / 8; }
 };
+
+// Workgroups of a launch per CU of its busiest part (an XCD of a single layer, an engine of several, or an XCD
+// too where a CU takes two workgroups, `shared`), for a layer of nf x nt tiles of which those from
+// feature tile live_nf on exit at once.  Beyond sixteen rounds the parts differ by little.
+inline float launch_load(int nf, int nt, int live_nf, int n_layers, bool shared = false) {
+  const float all = (float)live_nf * nt * n_layers / kChipCUs;
+  if (all > 16.f) return all;
+  TileGrid g;
+  const int slots = choose_tile_grid(nf, nt, g);
+  if (n_layers > 1) {
+    const ChipLoad load(g, slots, live_nf);
+    return shared ? load.busiest_xcd(n_layers) / 32.f : load.busiest(n_layers) / 8.f;
+  }
+  const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift);
+  const int supers = g.nsf * ((nt + gt - 1) / gt);
+  return (float)((supers + 7) / 8 * (gf < nf ? gf : nf) * (gt < nt ? gt : nt)) / (kChipCUs / 8);
+}
 
 // Split d_model loops for a partly filled last round (paper Section 4.1.1, "Performance
 // considerations": the projection's efficiency depends on how the token count fills the device).
@@ -213,27 +251,34 @@ constexpr float kSmallRoundUs = 3.f;
 // Tiles of 128 rows x 64 nb tokens (restore_mid.inc).  They add a token's channels up in the order of the
 // unsplit 256 x 256 tiles, so results do not depend on which of the two a launch takes.
 //
-// Cost of a round of 256 workgroups (512 for nb = 1 beyond the first 256: two share a CU), from token
-// sweeps of d_model 256 .. 8192, 8 .. 56 heads: kMidStepUs per 64 channels and 3 + 0.7 nb for
-// prologue and epilogue; a round of the large tiles takes 1.5 and 5.  Launches of several layers run
-// their rounds into each other (fractions of a round count; with these tiles from four rounds on: 8 layers
-// of 4096 onto 2048, 560 tokens, 1.5 rounds of nb = 3 take 107 us, the large tiles 97) and read every
-// layer's weights from memory: the hypotenuse with that time fits both kernels to 15 %, but for nb = 5, whose ring of two stages
-// does not cover the memory's latency (300 tokens, 8 layers of 5120 onto 10240: 368 us against 308), and
-// which LayerNorm's extra matrix ops make slower than the large tiles (558 tokens of 7168 onto 14336:
-// 167 us against 153).  A single layer takes nb = 1 up to 512 workgroups only: beyond, the pairs lose step and
-// with it the L2 (those 558 tokens, 1008 workgroups: 259 us).  The figures are good to a few percent, so these tiles have to promise 5 %.
+// A launch takes as many rounds as its busiest XCD (several layers: its busiest shader engine, see ChipLoad), one
+// workgroup per CU.  Cost of a round, fitted on the times of every kernel at 8600 random shapes (d_model
+// 64 .. 8192, 1 .. 128 heads, 1 .. 32768 tokens, one layer or 2 .. 32): kMidStepUs per 64 channels and
+// 2.5 + 0.75 nb for prologue and epilogue; nb = 1 beyond one workgroup per CU (two share one) 0.48 per 64 channels
+// and workgroup, prologue and epilogue behind the other's loop; the large tiles 1.09 and up to 0.45 more as
+// the CUs fill up, a tenth less where rounds follow each other, and 4.7.  The hypotenuse of that and the time of the
+// weights (7.7 TB/s, in part from the caches) is the cost; single-layer calls of the large tiles come
+// out without the weights, split ones 6 % above plan_split's figures.
+// Not taken: nb = 5 in launches of several layers, where its ring of two stages does not cover the
+// memory's latency (300 tokens, 8 layers of 5120 onto 10240: 368 us against 308), and with LayerNorm, whose extra matrix
+// ops make it slower than the large tiles (558 tokens of 7168 onto 14336: 167 us against 153); nb = 1
+// beyond two workgroups per CU in a single layer (the pairs lose step and with it the L2: those 558 tokens
+// 259 us), six in several (24 layers of 1600 onto 6400, 266 tokens: 374 us against 261).
+// The figures are good to 9 % or so, so these tiles have to promise that.  Over those shapes the choice
+// takes 0.3 % (one layer) and 1.9 % (several) longer than the fastest kernel in the mean, and 22 are more than 4 %
+// slower than the large tiles; workgroups counted over the whole chip instead of its busiest part
+// made that 166 (20 layers of 4096 onto 2048, 179 tokens 136 us against 99; 8627 tokens of 7872 onto 128 108 against 65).
 // Measured, these tiles against the large ones (whole or split): one layer of 4096 onto 2048, 800 tokens
 // 25.5 / 44.0 us, 4000 tokens 62.9 / 90.9, 6000 tokens 98.4 / 99.6 (not taken); 5120 onto 10240, 300
 // tokens 52.8 / 62.9, 900 99.0 / 120, 1200 147 / 123 (not taken); 32 layers of 4096 onto 2048, 40
 // tokens 111 / 126, 256 tokens 181 / 147 (not taken).
-constexpr float kMidStepUs[6] = {0.f, 0.40f, 0.58f, 0.77f, 0.98f, 1.20f};
-constexpr float kMidPairStepUs = 0.65f;                  // nb = 1, two workgroups on a CU
-// a round of large tiles that leaves every XCD some of its 32 CUs free (at most 20, 24 tiles on the busiest):
-// 4096 onto 8192 features, 1200 tokens 80 us; 7168 onto 14336, 558 tokens 151; against 1.5 per 64 channels
-// (below d_model 1024 prologue and epilogue hide the difference)
-constexpr float kWholeStepPart20Us = 1.2f, kWholeStepPart24Us = 1.3f;
-constexpr float kTileFixedUs = 5.f, kWeightsUsPerByte = 1.f / 5.4e6f;
+constexpr float kMidStepUs[6] = {0.f, 0.41f, 0.57f, 0.725f, 0.835f, 1.29f};
+constexpr float kMidSharedStepUs = 0.48f;                // nb = 1, two workgroups on a CU
+constexpr float kMidFixedUs = 2.5f, kMidBlockUs = 0.75f, kMidPromise = 1.09f;
+constexpr float kTileStepUs = 1.09f, kTileStepBusyUs = 0.45f, kTileNextRounds = 0.91f, kTileFixedUs = 4.7f;
+constexpr float kSplitPrice = 1.06f;
+constexpr float kWeightsUsPerByte = 1.f / 7.7e6f;
+constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token kernel and split tiles read them
 
 struct Route {
   enum Kind { kTiles, kSmall, kMid } kind = kTiles;
@@ -246,45 +291,43 @@ struct Route {
 // sums may depend on the token count (split launches allowed); the few-token kernel and split plans need it.
 inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool layer_norm, bool free_order) {
   const int nm = d_model / (2 * kTileK);
-  const float weights_us = 4.f * d_kv * d_model * kWeightsUsPerByte;
-  const float all_weights_us = weights_us * n_layers;
+  const float weights = 4.f * d_kv * d_model;              // bytes of a layer
+  const float few_weights_us = weights * kFewWeightsUsPerByte, weights_us = weights * n_layers * kWeightsUsPerByte;
   Route route;
 
   // the 256 x 256 tiles, whole or split
   const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF, nt = (n_tok + kTileT - 1) / kTileT;
-  const float tiles = (float)nf * nt * n_layers / kChipCUs;
   float best;
-  if (n_layers > 1) {
-    const float t = (kWholeStepUs * nm + kTileFixedUs) * (tiles > 1.f ? tiles : 1.f);
-    best = sqrtf(t * t + all_weights_us * all_weights_us);
-  } else {
+  if (n_layers == 1 && free_order) {
     SplitPlan& sp = route.split_plan;
-    TileGrid& g = route.grid;
-    choose_tile_grid(nf, nt, g);
-    const int gf = 1 << g.gf_shift, gt = 1 << (g.g_shift - g.gf_shift);
-    const int supers = g.nsf * ((nt + gt - 1) / gt);
-    const int busiest = (supers + 7) / 8 * (gf < nf ? gf : nf) * (gt < nt ? gt : nt);   // tiles of the busiest XCD
-    const float step_us = nm < 16 ? kWholeStepUs : busiest <= 20 ? kWholeStepPart20Us : busiest <= 24 ? kWholeStepPart24Us : kWholeStepUs;
-    best = (step_us * nm + kTileFixedUs) * ceilf(tiles);
-    route.split = free_order && plan_split(nf, nt, nm, false, sp, g);
+    route.split = plan_split(nf, nt, nm, false, sp, route.grid);
     if (route.split) {
       const int rest = n_tok - sp.nt_main * kTileT;      // tokens of the split tiles
       const float live = (float)round_up(rest, 16) / ((nt - sp.nt_main) * kTileT);
       float loop = 1.1f * kSplitStepUs * nm / sp.n_split;   // with most CUs busy
-      if (loop < weights_us) loop = weights_us;
-      best = kWholeStepUs * nm * (nf * nt / kChipCUs) + loop + kSplitSlotUs * sp.n_tail * sp.n_split * live + kSplitFixedUs + kTileFixedUs;
+      if (loop < few_weights_us) loop = few_weights_us;
+      best = kSplitPrice * (kWholeStepUs * nm * (nf * nt / kChipCUs) + loop + kSplitSlotUs * sp.n_tail * sp.n_split * live + kSplitFixedUs + kTileFixedUs);
     }
   }
+  if (!route.split) {
+    const float load = launch_load(nf, nt, nf, n_layers), rounds = ceilf(load);
+    const float step_us = (kTileStepUs + kTileStepBusyUs * (load / rounds)) * (rounds > 1.f ? kTileNextRounds : 1.f);
+    best = rounds * (step_us * nm + kTileFixedUs);
+    if (n_layers > 1) best = sqrtf(best * best + weights_us * weights_us);
+  }
 
-  const int groups = d_kv / kPairGroup;
+  const int groups = d_kv / kPairGroup, groups_pad = round_up(d_kv, kPartAlign) / kPairGroup;
   for (int b = 1; b <= (n_layers > 1 || layer_norm ? 4 : 5); ++b) {
-    const float wgs = (float)groups * ((n_tok + 64 * b - 1) / (64 * b)) * n_layers / kChipCUs;
-    const bool pair = b == 1 && wgs > 1.f;
-    if (pair && n_layers == 1 && wgs > 2.f) continue;
-    float rounds = pair ? wgs / 2 : wgs;
-    if (n_layers == 1 || rounds < 4.f) rounds = ceilf(rounds);
-    float t = 1.05f * rounds * ((pair ? kMidPairStepUs : kMidStepUs[b]) * nm + 3.f + 0.7f * b);
-    if (n_layers > 1) t = sqrtf(t * t + all_weights_us * all_weights_us);
+    auto cost = [&](float wgs) {                           // workgroups per CU of the busiest part
+      const float loop_us = b == 1 && wgs > 1.f ? ceilf(wgs) * kMidSharedStepUs * nm
+                                                : ceilf(wgs) * (kMidStepUs[b] * nm + kMidFixedUs + kMidBlockUs * b);
+      return kMidPromise * sqrtf(loop_us * loop_us + weights_us * weights_us);
+    };
+    const int nt_b = (n_tok + 64 * b - 1) / (64 * b);
+    if (b > 1 && cost((float)groups * nt_b * n_layers / kChipCUs) >= best) continue;   // even if the parts were equally busy
+    const float wgs = launch_load(groups_pad, nt_b, groups, n_layers, b == 1);
+    if (b == 1 && wgs > (n_layers > 1 ? 6.f : 2.f)) continue;
+    const float t = cost(wgs);
     if (t < best) { best = t; route.kind = Route::kMid; route.nb = b; }
   }
 
@@ -299,7 +342,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
       const float t = 2.85e-5f * d_model * in_turn * (32 + 16 * b) + kSmallRoundUs * (rounds - 1.f);
       if (b == 1 || t < stream_us) { stream_us = t; nb = b; }
     }
-    const float t = 3.5f + sqrtf(stream_us * stream_us + weights_us * weights_us);
+    const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
     if (t < best) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
   if (route.kind != Route::kTiles) route.split = false;
@@ -353,7 +396,9 @@ struct LayerEntry {
 // 32 tiles (a short context), up to as many layers as would fill one round of 256 workgroups, at most 32:
 // a launch takes a round's time however few of the CUs it uses.  Such a layer's tiles lie on few XCDs,
 // consecutive layers on consecutive ones, so a launch can take two rounds with CUs free elsewhere; the count
-// is the one with the fewest rounds over all launches of the call, and of those with the fewest launches.
+// is the one with the fewest rounds over all launches of the call, of those with the fewest launches, and
+// of those a multiple of eight, which loads the XCDs evenly (24 layers of 20 tiles: three times eight, not
+// 11 + 11 + 2), or else the largest.
 // 32 layers of 4096 onto 2048, 600 tokens (24 tiles a layer): 578 us in tens, which take two rounds each
 // but for the last two layers, 381 in eights, which take one; 10 layers of 640 onto 5632, 239 tokens (22
 // tiles): 36.8 us in one launch of two rounds, 56.8 as 8 + 2; 20 of 128 onto 1536, 271 tokens: 27.1 in
@@ -367,10 +412,12 @@ inline int layers_per_launch(int nf, int nt, int n_layers) {
   TileGrid g;
   const int slots = choose_tile_grid(nf, nt, g);
   const ChipLoad load(g, slots, nf);
-  int best = 0, best_rounds = 0;
+  int best = 0, best_rounds = 0, best_launches = 0;
   for (int n = most; n >= 8; --n) {
-    const int rounds = n_layers / n * load.rounds(n) + load.rounds(n_layers % n);
-    if (best == 0 || rounds < best_rounds) { best = n; best_rounds = rounds; }
+    const int launches = (n_layers + n - 1) / n, rounds = n_layers / n * load.rounds(n) + load.rounds(n_layers % n);
+    if (best == 0 || rounds < best_rounds || (rounds == best_rounds && launches <= best_launches && n % 8 == 0 && best % 8 != 0)) {
+      best = n; best_rounds = rounds; best_launches = launches;
+    }
   }
   return best;
 }

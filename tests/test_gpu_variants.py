@@ -138,14 +138,13 @@ def test_opt30b_shape(hc):
     ctx.destroy()
 
 
-@pytest.mark.parametrize("norm_kind,n_kv,per_launch,kernel_by_rule",
-                         [(0, 2, 32, "rows128"), (1, 2, 32, "rows128"), (1, 16, 16, "tiles")])
-def test_layers_in_one_launch(hc, norm_kind, n_kv, per_launch, kernel_by_rule):
+@pytest.mark.parametrize("norm_kind,n_kv,per_launch", [(0, 2, 32), (1, 2, 32), (1, 16, 16)])
+def test_layers_in_one_launch(hc, norm_kind, n_kv, per_launch):
     """hc_restore_kv_layers over 35 layers (more than one launch holds; layers with and without
     a bias, so the kernel mode changes along the way) writes bit for bit what one
-    hc_restore_kv per layer writes, and that is the oracle's result; on the kernel that the launch rule
-    takes, and on the 256 x 256 tiles, whose second token tile is ragged, that a context gets which asks
-    for split launches."""
+    hc_restore_kv per layer writes, and that is the oracle's result; on the tiles of 128 rows that
+    the launch rule takes, and on the 256 x 256 tiles, whose second token tile is ragged, that a context gets
+    which asks for split launches."""
     import torch
     rng = np.random.default_rng([9, norm_kind] if n_kv == 2 else [9, norm_kind, n_kv])
     L, d_model, hd, B, T = 35, 256, 64, 16, 300
@@ -180,7 +179,7 @@ def test_layers_in_one_launch(hc, norm_kind, n_kv, per_launch, kernel_by_rule):
         ctx.set_kv_pool(l, pools_a[l], num_pages)
         ctx.restore_kv(l, hidden[l], d_pos, T, d_bt, n_blocks, s)
     # two or sixteen tiles per layer: so many layers go into one launch (short contexts fill the chip with layers)
-    for mode, kernel in ((2, "tiles"), (1, kernel_by_rule)):
+    for mode, kernel in ((2, "tiles"), (1, "rows128")):
         assert hc.diag_route(d_model, d_kv, T, L, norm_kind, mode)[::3] == (kernel, per_launch)
         ctx.set_split(mode)
         for l in range(L):

@@ -438,12 +438,10 @@ int main() {
         const ChipLoad load(g, slots, live);
         int count[32] = {};
         for (int l = 0; l < 33; ++l) {
-          for (int per_cu = 1; per_cu <= 2; ++per_cu) {
-            int most = 0;
-            for (int c : count) most = c > most ? c : most;
-            bad += load.rounds(l, per_cu) != (most + 8 * per_cu - 1) / (8 * per_cu);
-            ++n;
-          }
+          int most = 0;
+          for (int c : count) most = c > most ? c : most;
+          bad += load.busiest(l) != most;
+          ++n;
           for (int w = 0; w < slots; ++w) {
             int f, t;
             const int id = l * slots + w;
@@ -461,3 +459,44 @@ int main() {
                     str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+# Measured on MI355X, weights not lately read: (d_model, d_kv, tokens, layers in the call or 0 for a single-layer call,
+# LayerNorm, us on the 256 x 256 tiles (whole or split), [us on tiles of 128 rows x 64, 128, .. 320 tokens])
+ROWS128_TIMES = [
+    (7872, 64, 8627, 0, 0, 65.36, [107.52, 79.21, 97.24, 117.34, 183.67]),
+    (5312, 2304, 217, 6, 1, 112.76, [154.88, 151.82, 183.74, 165.87, 233.05]),
+    (192, 192, 13144, 0, 1, 14.6, [14.24, 16.59, 21.33, 14.81, 16.77]),
+    (64, 1280, 455, 4, 1, 13.63, [12.87, 15.06, 18.84, 14.84, 16.46]),
+    (768, 576, 6802, 0, 0, 27.53, [31.73, 37.22, 33.3, 37.91, 26.06]),
+    (4096, 1024, 179, 20, 0, 99.33, [136.33, 127.88, 119.94, 133.79, 199.46]),
+    (7168, 576, 226, 20, 1, 160.41, [208.39, 198.08, 222.4, 214.1, 316.01]),
+    (1088, 576, 714, 3, 0, 27.65, [20.74, 36.49, 31.65, 35.74, 41.33]),
+    (8192, 1024, 138, 20, 1, 200.49, [259.18, 242.33, 212.47, 245.01, 344.6]),
+    (4800, 576, 765, 3, 0, 88.8, [65.64, 114.52, 93.85, 109.44, 132.34]),
+    (8192, 1024, 616, 5, 1, 171.16, [192.78, 204.72, 183.28, 219.97, 145.78]),
+    (4096, 1024, 144, 20, 0, 103.69, [132.68, 123.67, 115.17, 127.99, 190.78]),
+    (8192, 1024, 395, 9, 1, 175.8, [220.66, 217.69, 200.11, 232.66, 333.92]),
+    (8192, 1024, 637, 6, 0, 165.17, [208.2, 203.96, 183.15, 206.23, 170.66]),
+    (192, 64, 89, 9, 0, 13.89, [8.35, 11.54, 12.8, 14.04, 15.38]),
+    (1600, 768, 5, 4, 0, 32.29, [14.85, 16.54, 18.81, 21.57, 25.35]),
+    (1088, 960, 1, 2, 0, 23.64, [11.4, 12.19, 13.95, 15.87, 18.29]),
+    (128, 192, 558, 13, 0, 18.5, [12.02, 14.86, 15.43, 16.38, 16.73]),
+    (64, 256, 80, 0, 0, 8.98, [4.9, 6.77, 8.15, 8.81, 10.06]),
+    (192, 448, 117, 0, 0, 11.02, [5.02, 6.83, 8.03, 9.13, 9.92]),
+    (256, 256, 147, 0, 0, 11.97, [6.11, 8.39, 10.53, 12.01, 13.45]),
+    (5504, 256, 47, 24, 0, 104.65, [46.86, 54.36, 61.98, 72.49, 85.54]),
+]
+
+
+def test_tiles_of_128_rows_only_where_they_were_measured_faster(hc):
+    """The launch rule against measured times: launches whose busiest XCD or shader engine needs a round more than
+    the chip as a whole would, and some that the tiles of 128 rows are there for.  The chosen kernel takes at
+    most 1.05 of the large tiles' time, and at most 1.1 of the fastest's where that is 128-row tiles by far."""
+    for d_model, d_kv, n_tok, n_layers, norm, tiles_us, rows_us in ROWS128_TIMES:
+        kernel, blocks, _, _ = hc.diag_route(d_model, d_kv, n_tok, n_layers, norm)
+        assert kernel != "few"
+        us = tiles_us if kernel == "tiles" else rows_us[blocks - 1]
+        where = (d_model, d_kv, n_tok, n_layers, norm, kernel, blocks, us, tiles_us, rows_us)
+        assert us <= 1.05 * tiles_us, where
+        assert min(rows_us) > 0.7 * tiles_us or us <= 1.1 * min(rows_us), where
