@@ -150,7 +150,9 @@ hc_status hc_restore_kv(hc_ctx* ctx, int32_t layer, const void* d_hidden,
  * layers have fewer than 32 tiles of 256 features x 256 tokens: up to as many layers as fill the 256
  * compute units once, at most 32), which removes the gaps between per-layer kernels and lets the
  * compute units run out of step.
- * Per layer the result is identical to hc_restore_kv's.  Every layer needs weights and a
+ * Per layer the result is hc_restore_kv's bit for bit under hc_set_split(ctx, 0); in the default mode a
+ * single layer may go to a split launch or to the few-token kernel (see hc_set_split), which add a token's
+ * channels up in another fp32 order: the same values within tolerance.  Every layer needs weights and a
  * pool (HC_ESTATE).  The pointer array is read during the call only. */
 hc_status hc_restore_kv_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
                                const void* const* h_d_hidden, const int32_t* d_positions,
@@ -393,9 +395,9 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * each other through an event, whatever their streams.  mode 0: never split.  mode 2: split
  * whenever the shape allows it (tests and measurements), and 256 x 256 tiles in every launch.
  * Launches over several layers (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
- * a kernel of its own when that is faster than whole or split tiles (up to 500 tokens or so
- * with few heads, 50 with many); its workgroups' waves share the d_model loop, so the same holds
- * for its results; it uses no workspace and one launch.  In modes 0 and 1 launches that whole tiles
+ * a kernel of its own when that is estimated faster than whole or split tiles (up to some 1500 to 2000 tokens
+ * with one or two heads of 128, 500 with 8, 130 with 32, 30 to 60 with 56); its workgroups' waves share the
+ * d_model loop, so the same holds for its results; it uses no workspace and one launch.  In modes 0 and 1 launches that whole tiles
  * fill badly (a short context, a device partly idle) go to tiles of 128 features x 64..320 tokens,
  * whose results are those of the unsplit 256 x 256 tiles bit for bit. */
 hc_status hc_set_split(hc_ctx* ctx, int32_t mode);

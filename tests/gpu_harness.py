@@ -149,3 +149,23 @@ class LayerCase:
     @property
     def x(self):
         return syn.bf16_bits_to_f64(self.x_bits)
+
+
+def restore_whole_tiles(ctx, layer, d_hidden, d_pos, n_tok, d_table, n_blocks, stream):
+    """One layer on the 256 x 256 tiles, every one of them whole: launches over several layers never split, and
+    a context that asks for split launches gets these tiles in every launch."""
+    ctx.set_split(2)
+    ctx.restore_kv_layers(layer, [d_hidden], d_pos, n_tok, d_table, n_blocks, stream)
+
+
+def assert_same_but_for_order(got_bits, want_bits):
+    """Results of two kernels that add the same fp32 products up in another order: the same elements written, and
+    every value within one bf16 step, or, for values that are small because their terms cancel,
+    within 2^-9 of the RMS of all values."""
+    m = want_bits != SENTINEL
+    assert np.array_equal(got_bits != SENTINEL, m)
+    fa, fb = syn.bf16_bits_to_f64(got_bits[m]), syn.bf16_bits_to_f64(want_bits[m])
+    step = np.maximum(np.abs(fa), np.abs(fb)) * 2.0 ** -7          # one bf16 step at the larger magnitude
+    bad = np.abs(fa - fb) > np.maximum(step, np.sqrt(np.mean(fb * fb)) * 2.0 ** -9)
+    assert not bad.any(), int(bad.sum())
+    return m

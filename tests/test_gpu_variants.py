@@ -224,6 +224,52 @@ def test_layers_in_one_launch(hc, norm_kind, n_kv, per_launch):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("norm_kind,T", [(0, 37), (1, 130), (0, 700)])
+def test_layers_against_single_calls_at_d_model_2048(hc, norm_kind, T):
+    """hc_restore_kv_layers at a width where single-layer calls of a short context go to the few-token kernel
+    by default and to split launches on request: bit for bit hc_restore_kv's result with splitting off, the same
+    but for the order of the sums in the other modes."""
+    import torch
+    L, d_model, n_kv, hd, B = 3, 2048, 2, 128, 16
+    d_kv, n_blocks = n_kv * hd, -(-T // B)
+    num_pages = n_blocks + 3
+    assert hc.diag_route(d_model, d_kv, T, 0, norm_kind)[0] == "few"
+    assert hc.diag_route(d_model, d_kv, T, 0, norm_kind, 2)[2] == 4
+    assert hc.diag_route(d_model, d_kv, T, L, norm_kind)[0] == "rows128"
+    desc = gh.make_desc(hc, n_layers=L, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd,
+                        block_size=B, max_position=T, norm_kind=norm_kind)
+    rng = np.random.default_rng([71, norm_kind, T])
+    ctx, s = hc.Context(desc), gh.stream_handle()
+    d_pos, d_bt = gh.to_dev_i32(rng.permutation(T)), gh.to_dev_i32(rng.permutation(num_pages)[:n_blocks])
+    hidden, keep = [], []
+    for l in range(L):
+        keep += [gh.to_dev_bf16(bf16(rng, (2 * d_kv, d_model), 0, 0.02)), gh.to_dev_bf16(bf16(rng, (d_model,), 1, 0.1))]
+        ctx.set_layer_weights(l, keep[-2], keep[-1], s)
+        hidden.append(gh.to_dev_bf16(bf16(rng, (T, d_model), 0.3, 1.0)))
+
+    def pools():
+        new = [gh.new_pool(num_pages, B, n_kv, hd) for _ in range(L)]
+        for l in range(L):
+            ctx.set_kv_pool(l, new[l], num_pages)
+        return new
+
+    for mode in (0, 1, 2):
+        ctx.set_split(mode)
+        together = pools()
+        ctx.restore_kv_layers(0, hidden, d_pos, T, d_bt, n_blocks, s)
+        assert ctx.poll_device_error(s) == 0
+        alone = pools()
+        for l in range(L):
+            ctx.restore_kv(l, hidden[l], d_pos, T, d_bt, n_blocks, s)
+        assert ctx.poll_device_error(s) == 0
+        for a, b in zip(together, alone):
+            if mode == 0:
+                assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+            m = gh.assert_same_but_for_order(gh.pool_bits(b), gh.pool_bits(a))
+            assert m.sum() == 2 * T * d_kv
+    ctx.destroy()
+
+
 def test_opt_style_ragged_and_streamed(hc):
     """OPT-style layers through the other entry points: a ragged batch of four contexts in one
     launch, and a whole-context pipelined restore from the chunk store."""
