@@ -25,8 +25,9 @@ def torch():
 
 
 def run_single(hc, torch, case, desc, positions, block_table, num_pages, layer=0, split=None):
+    """One hc_restore_kv call under split mode `split` (None: the default), or, "whole", on whole 256 x 256 tiles."""
     ctx = hc.Context(desc)
-    if split is not None:
+    if split not in (None, "whole"):
         ctx.set_split(split)
     pool = gh.new_pool(num_pages, desc.block_size, desc.n_kv_heads, desc.head_dim)
     s = gh.stream_handle()
@@ -35,7 +36,10 @@ def run_single(hc, torch, case, desc, positions, block_table, num_pages, layer=0
     ctx.set_kv_pool(layer, pool, num_pages)
     d_x = gh.to_dev_bf16(case.x_bits) if len(case.x_bits) else None
     d_pos, d_bt = gh.to_dev_i32(positions), gh.to_dev_i32(block_table)
-    ctx.restore_kv(layer, d_x, d_pos, len(positions), d_bt, len(block_table), s)
+    if split == "whole":
+        gh.restore_whole_tiles(ctx, layer, d_x, d_pos, len(positions), d_bt, len(block_table), s)
+    else:
+        ctx.restore_kv(layer, d_x, d_pos, len(positions), d_bt, len(block_table), s)
     flags = ctx.poll_device_error(s)
     bits = gh.pool_bits(pool)
     ctx.destroy()
@@ -203,23 +207,24 @@ def test_split_and_unsplit_launches_agree_on_random_shapes(hc, torch):
               f"{plan['n_split']}; {np.mean(a[m] == b[m]):.4f} of the values bit-identical", flush=True)
 
 
-@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,style,norm", [
-    (1024, 2, 64, 1, 0, 0),        # one token; two supersteps of the loop per wave
-    (1088, 3, 64, 16, 1, 0),       # 17 supersteps over eight waves; padded K/V parts
-    (4096, 8, 128, 17, 0, 0),
-    (1600, 2, 192, 33, 1, 0),      # pair groups that straddle the tile's heads
-    (2048, 16, 128, 49, 0, 0),
-    (1024, 40, 128, 50, 2, 0),     # several workgroups per CU
-    (2048, 1, 256, 130, 0, 0),
-    (4096, 8, 128, 201, 0, 0),     # four blocks of tokens per workgroup, ragged last one
-    (1472, 5, 128, 47, 0, 1),      # LayerNorm
-    (4096, 4, 64, 240, 2, 1),
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,style,norm,blocks", [
+    (1024, 2, 64, 1, 0, 0, 1),     # one token; two supersteps of the loop per wave
+    (1088, 3, 64, 16, 1, 0, 1),    # 17 supersteps over eight waves; padded K/V parts
+    (4096, 8, 128, 17, 0, 0, 1),
+    (1600, 2, 192, 33, 1, 0, 1),   # pair groups that straddle the tile's heads
+    (2048, 16, 128, 49, 0, 0, 2),
+    (1024, 40, 128, 50, 2, 0, 2),  # several workgroups per CU
+    (2048, 1, 256, 130, 0, 0, 1),
+    (1088, 32, 128, 33, 0, 0, 3),
+    (4096, 8, 128, 201, 0, 0, 4),  # four blocks of tokens per workgroup, ragged last one
+    (1472, 5, 128, 47, 0, 1, 1),   # LayerNorm
+    (4096, 4, 64, 240, 2, 1, 1),
 ])
-def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm):
+def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm, blocks):
     """Layers that the few-token kernel takes, at the edges of its token blocks and loop shares:
-    against the CPU model of the arithmetic (RMSNorm), and against the kernel of whole tiles
-    within one bf16 step, or, for values that are small because their terms cancel, 2^-9 of the
-    RMS of all values (the order of fp32 additions is what differs)."""
+    against the CPU model of the arithmetic (RMSNorm), and against whole 256 x 256 tiles but for the order of the
+    fp32 additions."""
+    assert hc.diag_route(d_model, n_kv * hd, n_tok, 0, norm)[:2] == ("few", blocks)
     rng = np.random.default_rng([77, d_model, n_kv, hd, n_tok, style, norm])
     case = gh.LayerCase(rng, d_model, n_kv, hd, n_tok)
     B, offset = 16, 40
@@ -230,15 +235,68 @@ def test_few_tokens(hc, torch, d_model, n_kv, hd, n_tok, style, norm):
     desc = gh.make_desc(hc, n_layers=1, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd,
                         block_size=B, max_position=offset + n_tok, rope_style=style, norm_kind=norm)
     bits, flags = run_single(hc, torch, case, desc, pos, bt, num_pages)
-    whole, flags0 = run_single(hc, torch, case, desc, pos, bt, num_pages, split=0)
+    whole, flags0 = run_single(hc, torch, case, desc, pos, bt, num_pages, split="whole")
     assert flags == 0 and flags0 == 0
     if norm == 0:
         gh.assert_close_to_model(bits, gh.model_pool(desc, case.x, case.gamma, case.wkv, pos, bt, num_pages))
-    m = whole != gh.SENTINEL
-    assert np.array_equal(bits != gh.SENTINEL, m) and m.sum() == 2 * n_tok * n_kv * hd
-    fa, fb = syn.bf16_bits_to_f64(bits[m]), syn.bf16_bits_to_f64(whole[m])
-    step = np.maximum(np.abs(fa), np.abs(fb)) * 2.0 ** -7
-    assert np.all(np.abs(fa - fb) <= np.maximum(step, np.sqrt(np.mean(fb * fb)) * 2.0 ** -9))
+    m = gh.assert_same_but_for_order(bits, whole)
+    assert m.sum() == 2 * n_tok * n_kv * hd
+
+
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,style,norm,blocks", [
+    (1024, 1, 64, 17, 2, "layer", 1),
+    (1472, 5, 128, 47, 1, "bias", 1),
+    (1024, 5, 64, 201, 0, "layer", 2),
+    (1024, 5, 64, 201, 1, "bias", 2),
+    (1088, 32, 128, 33, 1, "layer", 3),
+    (1088, 32, 128, 33, 2, "bias", 3),
+    (1024, 8, 128, 201, 2, "layer", 4),
+    (1024, 16, 64, 201, 0, "bias", 4),
+])
+def test_few_tokens_variants_and_bad_rows(hc, torch, d_model, n_kv, hd, n_tok, style, norm, blocks):
+    """The few-token kernel's other epilogues (LayerNorm with shift and bias, RMSNorm with a K/V bias) for every count
+    of token blocks, with a row whose position lies past max_position and the rows of a page that the pool does not have:
+    flags and written elements of whole 256 x 256 tiles, values but for the order of the sums, and as a
+    ragged batch of two contexts the same bits again."""
+    layer_norm = norm == "layer"
+    assert hc.diag_route(d_model, n_kv * hd, n_tok, 0, layer_norm)[:2] == ("few", blocks)
+    torch.manual_seed(d_model * 7919 + n_tok)
+    rows, B, offset = 2 * n_kv * hd, 16, 40
+    n_blocks = (offset + n_tok + B - 1) // B
+    num_pages = n_blocks + 3
+    desc = gh.make_desc(hc, n_layers=1, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                        max_position=offset + n_tok, rope_style=style, norm_kind=int(layer_norm))
+    ctx, s = hc.Context(desc), gh.stream_handle()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    w, gain = torch.randn((rows, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+    shift = 0.1 * torch.randn(d_model, **bf) if layer_norm else None
+    bias = 0.1 * torch.randn(rows, **bf)
+    ctx.set_layer_weights_affine(0, w, gain, shift, bias, s)
+    x = torch.randn((n_tok, d_model), **bf) + 0.25
+    pos = torch.arange(offset, offset + n_tok, dtype=torch.int32, device="cuda")
+    pos[n_tok // 2] = offset + n_tok
+    table = torch.randperm(num_pages, device="cuda")[:n_blocks].to(torch.int32)
+    table[-1] = num_pages
+    cu = torch.tensor([0, n_tok // 3, n_tok], dtype=torch.int32, device="cuda")
+    tables = torch.stack([table, table])
+
+    def outcome(call):
+        pool = gh.new_pool(num_pages, B, n_kv, hd)
+        ctx.set_kv_pool(0, pool, num_pages)
+        ctx.set_split(1)
+        call()
+        return ctx.poll_device_error(s), gh.pool_bits(pool)
+
+    flags, few = outcome(lambda: ctx.restore_kv(0, x, pos, n_tok, table, n_blocks, s))
+    whole_flags, whole = outcome(lambda: gh.restore_whole_tiles(ctx, 0, x, pos, n_tok, table, n_blocks, s))
+    ragged_flags, ragged = outcome(lambda: ctx.restore_kv_ragged(0, x, pos, n_tok, cu, 2, tables, n_blocks, s))
+    assert flags == whole_flags == ragged_flags == (hc.HC_DEV_BAD_POSITION | hc.HC_DEV_BAD_PAGE)
+    at = torch.arange(offset, offset + n_tok, device="cuda")
+    bad = (at // B == n_blocks - 1) | (at == offset + n_tok // 2)
+    m = gh.assert_same_but_for_order(few, whole)
+    assert m.sum() == int((~bad).sum()) * rows
+    assert np.array_equal(ragged, few)
+    ctx.destroy()
 
 
 @pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm", [
