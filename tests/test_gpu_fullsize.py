@@ -212,7 +212,8 @@ def test_split_launch_whole_and_split_tiles(hc, name):
     tiles and split workgroups in one grid, then the finishing launch; tokens in scrambled
     order.  Exact written set, the random projection over every token, and every element of
     all tokens of the last, ragged row of token tiles (where the split tiles are) plus ~650
-    sampled tokens of the whole rows; then the same with splitting switched off."""
+    sampled tokens of the whole rows; then the same with every tile whole, and with splitting off, where
+    the launch rule may take the tiles of 128 rows."""
     import torch
     c = SPLIT_CASES[name]
     d_model, n_kv, hd, T, B = c["d_model"], c["n_kv"], c["hd"], c["T"], c["B"]
@@ -226,11 +227,15 @@ def test_split_launch_whole_and_split_tiles(hc, name):
     d_w, d_g, d_x = gh.to_dev_bf16(case.wkv_bits), gh.to_dev_bf16(case.gamma_bits), gh.to_dev_bf16(case.x_bits)
     ctx.set_layer_weights(0, d_w, d_g, s)
     d_pos, d_bt = gh.to_dev_i32(pos), gh.to_dev_i32(bt)
-    for split in (2, 0):
-        ctx.set_split(split)
+    assert hc.diag_route(d_model, n_kv * hd, T, mode=2)[::2] == ("tiles", plan["n_split"])
+    for split in (2, "whole", 0):
         pool = gh.new_pool(num_pages, B, n_kv, hd)
         ctx.set_kv_pool(0, pool, num_pages)
-        ctx.restore_kv(0, d_x, d_pos, T, d_bt, len(bt), s)
+        if split == "whole":
+            gh.restore_whole_tiles(ctx, 0, d_x, d_pos, T, d_bt, len(bt), s)
+        else:
+            ctx.set_split(split)
+            ctx.restore_kv(0, d_x, d_pos, T, d_bt, len(bt), s)
         assert ctx.poll_device_error(s) == 0
         torch.cuda.synchronize()
         res = check_layer(None, desc, gh.pool_bits(pool), case.x_bits, case.wkv_bits, case.gamma_bits, pos,

@@ -124,9 +124,9 @@ def test_shapes_against_oracle(hc, torch, d_model, n_kv, hd, n_tok, style):
                         rope_theta=500000.0)
     ora = oracle_single(case, desc, pos, bt, num_pages)
     model = gh.model_pool(desc, case.x, case.gamma, case.wkv, pos, bt, num_pages)
-    # as the library launches it by default; then, where the shape allows it, with the d_model
-    # loops of its tiles split (mode 2) and with every tile whole (mode 0)
-    modes = [None] + ([2, 0] if hc.diag_split_plan(d_model, n_kv * hd, n_tok, 2)["split"] else [])
+    # as the library launches it by default and without another order of sums (mode 0); on whole 256 x 256 tiles;
+    # where the shape allows it, with the d_model loops of these tiles split (mode 2)
+    modes = [None, 0, "whole"] + ([2] if hc.diag_split_plan(d_model, n_kv * hd, n_tok, 2)["split"] else [])
     for split in modes:
         bits, flags = run_single(hc, torch, case, desc, pos, bt, num_pages, split=split)
         assert flags == 0
@@ -146,8 +146,9 @@ SPLIT_SHAPES = [
 @pytest.mark.parametrize("d_model,n_kv,hd,n_tok,style,expect", SPLIT_SHAPES)
 def test_split_launch_against_oracle(hc, torch, d_model, n_kv, hd, n_tok, style, expect):
     """Launches that split the d_model loop of their tiles (split workgroups, then the finishing
-    launch), every element against the oracle.  A launch with whole tiles and split tiles in
-    one grid needs more than 256 tiles: tests/test_gpu_fullsize.py."""
+    launch), every element against the oracle; the same on whole tiles, and in the other split modes, where
+    the few-token kernel and the tiles of 128 rows take these shapes.  A launch with whole tiles and split
+    tiles in one grid needs more than 256 tiles: tests/test_gpu_fullsize.py."""
     plan = hc.diag_split_plan(d_model, n_kv * hd, n_tok, 2)
     assert plan["split"] == 1 and (plan["nt_main"], plan["n_tail"], plan["n_split"]) == expect, plan
     case, pos, bt, num_pages, offset = shape_inputs(d_model, n_kv, hd, n_tok, style)
@@ -155,7 +156,8 @@ def test_split_launch_against_oracle(hc, torch, d_model, n_kv, hd, n_tok, style,
                         head_dim=hd, block_size=16, max_position=offset + n_tok, rope_style=style,
                         rope_theta=500000.0)
     ora = oracle_single(case, desc, pos, bt, num_pages)
-    for split in (2, 1, 0):
+    assert [hc.diag_route(d_model, n_kv * hd, n_tok, mode=m)[0] for m in (2, 1, 0)] == ["tiles", "few", "rows128"]
+    for split in (2, "whole", 1, 0):
         bits, flags = run_single(hc, torch, case, desc, pos, bt, num_pages, split=split)
         assert flags == 0
         worst = gh.compare_pool(bits, ora)
@@ -167,8 +169,8 @@ def test_split_and_unsplit_launches_agree_on_random_shapes(hc, torch):
     one to twelve tiles split two to sixteen ways, all three RoPE styles): the split launch
     writes exactly the cache elements the unsplit launch writes, and every value within one
     bf16 step of it, or, for values that are small because their terms cancel, within 2^-9 of
-    the RMS of all values (the two differ only in the order of fp32 additions).  The unsplit
-    kernel is the one the other tests hold against the oracle at many shapes."""
+    the RMS of all values (the two differ only in the order of fp32 additions).  The unsplit launch
+    computes whole 256 x 256 tiles, which test_shapes_against_oracle holds against the oracle."""
     rng = np.random.default_rng(2024)
     done = 0
     while done < 20:
@@ -191,18 +193,13 @@ def test_split_and_unsplit_launches_agree_on_random_shapes(hc, torch):
         desc = gh.make_desc(hc, n_layers=1, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd,
                             block_size=B, max_position=offset + n_tok, rope_style=style)
         got = []
-        for split in (2, 0):
+        for split in (2, "whole"):
             bits, flags = run_single(hc, torch, case, desc, pos, bt, num_pages, split=split)
             assert flags == 0
             got.append(bits)
         a, b = got
-        assert np.array_equal(a != gh.SENTINEL, b != gh.SENTINEL), (d_model, n_kv, hd, n_tok, style)
-        m = a != gh.SENTINEL
-        assert m.sum() == 2 * n_tok * n_kv * hd
-        fa, fb = syn.bf16_bits_to_f64(a[m]), syn.bf16_bits_to_f64(b[m])
-        step = np.maximum(np.abs(fa), np.abs(fb)) * 2.0 ** -7          # one bf16 step at the larger magnitude
-        bad = np.abs(fa - fb) > np.maximum(step, np.sqrt(np.mean(fb * fb)) * 2.0 ** -9)
-        assert not bad.any(), (d_model, n_kv, hd, n_tok, style, int(bad.sum()))
+        m = gh.assert_same_but_for_order(a, b)
+        assert m.sum() == 2 * n_tok * n_kv * hd, (d_model, n_kv, hd, n_tok, style)
         print(f"d_model {d_model} heads {n_kv} x {hd} tokens {n_tok} style {style}: {plan['n_tail']} tiles x "
               f"{plan['n_split']}; {np.mean(a[m] == b[m]):.4f} of the values bit-identical", flush=True)
 
@@ -299,29 +296,42 @@ def test_few_tokens_variants_and_bad_rows(hc, torch, d_model, n_kv, hd, n_tok, s
     ctx.destroy()
 
 
-@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm", [
-    (64, 1, 64, 1, 2, 0, "rms"),           # one token, one superstep of the loop, one workgroup
-    (256, 4, 64, 65, 3, 1, "rms"),         # one token in the second tile
-    (576, 3, 192, 130, 2, 0, "bias"),      # padded K/V parts, pair groups that straddle the packed tile's halves
-    (640, 43, 128, 140, 1, 0, "rms"),      # two token blocks per wave (one layer)
-    (128, 42, 128, 193, 1, 1, "layer"),
-    (64, 103, 64, 257, 1, 2, "bias"),      # three
-    (192, 43, 128, 387, 1, 0, "layer"),    # four
-    (512, 43, 128, 517, 1, 0, "rms"),      # five
-    (640, 43, 64, 75, 3, 0, "layer"),      # two token blocks per wave, several layers
-    (64, 77, 64, 140, 3, 1, "rms"),        # three
-    (192, 67, 64, 205, 3, 0, "bias"),      # four
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm,alone,together", [
+    # alone, together: token blocks per wave of a single-layer call and of the launch over all layers
+    (64, 1, 64, 1, 2, 0, "rms", 1, 1),           # one token, one superstep of the loop, one workgroup
+    (256, 4, 64, 65, 3, 1, "rms", 1, 1),         # one token in the second tile
+    (576, 3, 192, 130, 2, 0, "bias", 1, 1),      # padded K/V parts, pair groups that straddle the packed tile's halves
+    (640, 43, 128, 140, 1, 0, "rms", 1, 1),      # two workgroups on a CU
+    (128, 42, 128, 193, 1, 1, "layer", 1, 1),
+    (704, 9, 64, 1601, 1, 2, "rms", 2, 2),
+    (704, 5, 192, 1025, 1, 1, "layer", 2, 2),    # one token in the ninth tile
+    (64, 103, 64, 257, 1, 2, "bias", 3, 3),
+    (64, 86, 64, 321, 1, 0, "layer", 3, 3),
+    (192, 33, 128, 577, 1, 0, "layer", 4, 4),
+    (256, 51, 64, 769, 1, 1, "bias", 4, 4),      # one token in the fourth tile
+    (1024, 25, 64, 2501, 1, 0, "rms", 5, 5),
+    (704, 5, 64, 385, 3, 0, "layer", 1, 2),      # several layers: one token in the fourth tile
+    (704, 3, 64, 641, 3, 1, "bias", 1, 2),
+    (448, 8, 64, 513, 3, 1, "rms", 1, 3),
+    (448, 4, 64, 1025, 3, 2, "layer", 1, 3),
+    (640, 5, 128, 387, 3, 0, "bias", 1, 4),
+    (640, 5, 64, 900, 3, 1, "layer", 1, 4),
 ])
-def test_mid_tiles_equal_whole_tiles(hc, torch, d_model, n_kv, hd, n_tok, layers, style, norm):
+def test_mid_tiles_equal_whole_tiles(hc, torch, d_model, n_kv, hd, n_tok, layers, style, norm, alone, together):
     """Shapes that go to tiles of 128 rows x 64..320 tokens, at the edges of the tiles and rings: layer
     by layer, all layers at once and as a ragged batch, with two rows whose position and page are
-    invalid, bit for bit the 256 x 256 tiles' results and flags (below d_model 1024 a context that asks
-    for split launches gets whole tiles: nothing can be split)."""
+    invalid, bit for bit the 256 x 256 tiles' results and flags (a context that asks for split launches gets whole
+    tiles at these shapes: nothing can be split)."""
+    layer_norm = norm == "layer"
+    for mode in (0, 1):
+        assert hc.diag_route(d_model, n_kv * hd, n_tok, 0, layer_norm, mode)[:2] == ("rows128", alone)
+        assert hc.diag_route(d_model, n_kv * hd, n_tok, layers, layer_norm, mode)[::3] == ("rows128", layers)
+        assert hc.diag_route(d_model, n_kv * hd, n_tok, layers, layer_norm, mode)[1] == together
+    assert hc.diag_route(d_model, n_kv * hd, n_tok, 0, layer_norm, 2)[::2] == ("tiles", 1)
     torch.manual_seed(d_model * 7919 + n_tok)
     rows, B, offset = 2 * n_kv * hd, 16, 40
     desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
                         max_position=offset + n_tok, rope_style=style, norm_kind=1 if norm == "layer" else 0)
-    assert hc.diag_split_plan(d_model, n_kv * hd, n_tok, 2)["split"] == 0
     ctx, s = hc.Context(desc), gh.stream_handle()
     bf = dict(dtype=torch.bfloat16, device="cuda")
     n_blocks = (offset + n_tok + B - 1) // B
@@ -428,7 +438,8 @@ def test_ragged_batch_split_launch_with_bad_rows(hc, torch):
     """The ragged batch at d_model 2048 with the d_model loops split four ways (mode 2), so that
     the per-token lookups (context by row offset, page by block table) run in the workgroups of
     the finishing launch; one context's table has an unmapped block and one position lies past
-    the table: those rows are skipped and flagged, the rest matches the oracle.  Then unsplit."""
+    the table: those rows are skipped and flagged, the rest matches the oracle.  Then on the few-token kernel (mode
+    1) and on the tiles of 128 rows (mode 0)."""
     rng = np.random.default_rng(29)
     d_model, n_kv, hd, B = 2048, 2, 128, 16
     lens = np.array([37, 260, 1, 129, 300], dtype=np.int32)
@@ -465,7 +476,8 @@ def test_ragged_batch_split_launch_with_bad_rows(hc, torch):
     d_w, d_g, d_x = gh.to_dev_bf16(case.wkv_bits), gh.to_dev_bf16(case.gamma_bits), gh.to_dev_bf16(case.x_bits)
     ctx.set_layer_weights(0, d_w, d_g, s)
     d_pos, d_cu, d_tab = gh.to_dev_i32(pos), gh.to_dev_i32(cu), gh.to_dev_i32(tables)
-    for split in (2, 0):
+    for split, kernel in ((2, "tiles"), (1, "few"), (0, "rows128")):
+        assert hc.diag_route(d_model, n_kv * hd, T, mode=split)[0] == kernel
         ctx.set_split(split)
         pool = gh.new_pool(num_pages, B, n_kv, hd)
         ctx.set_kv_pool(0, pool, num_pages)
@@ -535,17 +547,15 @@ def test_host_side_errors(hc, torch):
 
 
 @pytest.mark.parametrize("pinned,loader,d_model", [(True, 0, 512), (True, 1, 512), (False, 0, 512), (True, 0, 2048)],
-                         ids=["copy-engines", "gather-kernel", "pageable-store", "split-launches"])
+                         ids=["copy-engines", "gather-kernel", "pageable-store", "few-token-kernel"])
 def test_restore_context_from_store(hc, torch, pinned, loader, d_model):
     """Whole-context pipelined restore from the chunk store: all layers, a token range that
     starts and ends inside chunks, positions offset so the first page is part filled; with
-    the gather-kernel loader, the hipMemcpyAsync loader, and a store in pageable memory.  At
-    d_model 2048 every layer's launch is a split launch (six tiles, four shares each, then the
-    finishing launch), so the loader's events interleave with two kernels per layer that
-    share the context's workspace."""
+    the gather-kernel loader, the hipMemcpyAsync loader, and a store in pageable memory; at d_model 512 on the
+    tiles of 128 rows, at 2048 on the few-token kernel."""
     rng = np.random.default_rng(31)
     L, n_kv, hd, B, CT = 5, 2, 128, 16, 64
-    assert hc.diag_split_plan(d_model, n_kv * hd, 650)["n_split"] == (4 if d_model == 2048 else 1)
+    assert hc.diag_route(d_model, n_kv * hd, 650)[0] == ("few" if d_model == 2048 else "rows128")
     T_stored, tok_begin, n_tok, pos_offset = 700, 30, 650, 1000
     desc = gh.make_desc(hc, n_layers=L, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv,
                         head_dim=hd, block_size=B, max_position=pos_offset + T_stored)
@@ -596,8 +606,10 @@ def test_restore_context_from_store(hc, torch, pinned, loader, d_model):
 
 
 def test_restore_context_from_store_split(hc, torch, monkeypatch):
-    """The same with split launches asked for, so that every layer's launch is one whatever the launch rules
-    prefer."""
+    """The same with split launches asked for: every layer's launch is one (six tiles, four shares each, then the
+    finishing launch), so the loader's events interleave with two kernels per layer that share the
+    context's workspace."""
+    assert hc.diag_route(2048, 256, 650, mode=2) == ("tiles", 0, 4, 1)
     plain = hc.Context
 
     def split_context(desc):

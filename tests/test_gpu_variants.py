@@ -39,7 +39,8 @@ VARIANTS = [
 def test_variant_matches_oracle(hc, norm_kind, rope_style, shift, with_bias):
     """Every element of a 3-tile x 3-tile problem with ragged tails (d_kv = 640 pads the K and
     V parts), rows with a clearly non-zero mean, unsorted positions; once with each of the 15
-    tiles' d_model loops split in two and finished by a second launch, once unsplit."""
+    tiles' d_model loops split in two and finished by a second launch, once on whole tiles, once on the
+    tiles of 128 rows."""
     rng = np.random.default_rng([5, norm_kind, rope_style, shift, with_bias])
     d_model, n_kv, hd, B, T = 1024, 5, 128, 16, 600
     d_kv = n_kv * hd
@@ -68,11 +69,16 @@ def test_variant_matches_oracle(hc, norm_kind, rope_style, shift, with_bias):
     oracle.restore_kv(ora, f(x), f(gamma), f(wkv), pos, bt,
                       beta=None if beta is None else f(beta), bias=None if bias is None else f(bias),
                       **gh.oracle_kw(desc))
-    for split in (2, 0):
-        ctx.set_split(split)
+    assert hc.diag_route(d_model, d_kv, T, 0, norm_kind, 0)[0] == "rows128"
+    for split in (2, "whole", 0):
         pool = gh.new_pool(num_pages, B, n_kv, hd)
         ctx.set_kv_pool(0, pool, num_pages)
-        ctx.restore_kv(0, gh.to_dev_bf16(x), gh.to_dev_i32(pos), T, gh.to_dev_i32(bt), n_blocks, s)
+        args = gh.to_dev_bf16(x), gh.to_dev_i32(pos), T, gh.to_dev_i32(bt), n_blocks, s
+        if split == "whole":
+            gh.restore_whole_tiles(ctx, 0, *args)
+        else:
+            ctx.set_split(split)
+            ctx.restore_kv(0, *args)
         assert ctx.poll_device_error(s) == 0
         worst = gh.compare_pool(gh.pool_bits(pool), ora)
         print(f"variant norm={norm_kind} rope={rope_style} shift={shift} bias={with_bias} split={split}: "
