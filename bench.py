@@ -109,8 +109,9 @@ def main():
                     help="diagnostic: override the workload's d_model (a multiple of 64) to separate the cost "
                          "per channel from the fixed cost per tile; implies a different synthetic shape")
     ap.add_argument("--split", type=int, default=1,
-                    help="hc_set_split mode for single-layer launches: 0 never split the d_model loop, "
-                         "1 (default) when the library's cost model says it pays, 2 whenever possible")
+                    help="hc_set_split mode: 0 every launch sums in channel order (no split tiles, no few-token "
+                         "kernel), 1 (default) the kernel the library's cost model prefers, 2 the 256 x 256 "
+                         "tiles, split in single-layer launches whenever possible")
     ap.add_argument("--tokens", type=int, default=None,
                     help="diagnostic: override the workload's token count (single-context workloads): short "
                          "contexts, where a layer fills only part of the chip")
@@ -168,6 +169,7 @@ def main():
         w = dataclasses.replace(w, n_q_heads=1, n_kv_heads=1, head_dim=128, tokens=256, n_seq=1,
                                 name=f"{w.name}-one-tile")
         args.layers_per_launch = 1
+        args.split = 2                                  # the 256 x 256 tiles, ...
     ragged = w.n_seq != 1
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
@@ -261,6 +263,8 @@ def main():
             if ragged:
                 ctx.restore_kv_ragged(l, hidden_dev[l], d_pos, T, d_cu, w.n_seq, d_bt, bt.shape[1],
                                       use[l % len(use)])
+            elif args.one_tile:                         # ... whole: the call over layers never splits
+                ctx.restore_kv_layers(l, hidden_dev[l:l + 1], d_pos, T, d_bt, len(bt), use[l % len(use)])
             else:
                 ctx.restore_kv(l, hidden_dev[l], d_pos, T, d_bt, len(bt), use[l % len(use)])
 
