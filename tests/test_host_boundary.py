@@ -368,6 +368,7 @@ def test_route_invariants(hc):
                         assert blocks in {"tiles": (0,), "few": (1, 2, 3, 4), "rows128": (1, 2, 3, 4, 5)}[kernel], where
                         assert mode != 2 or kernel == "tiles", where
                         assert kernel != "few" or (mode == 1 and d_model >= 1024), where
+                        assert blocks < 5 or norm == hc.HC_NORM_RMS, where
                         for n_layers in (1, 3, 8, 40):
                             kernel, blocks, ways, layers = hc.diag_route(d_model, d_kv, n_tok, n_layers, norm, mode)
                             assert kernel != "few" and ways == 1 and min(n_layers, 8) <= layers <= min(n_layers, 32)
