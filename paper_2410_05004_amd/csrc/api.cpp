@@ -522,7 +522,7 @@ hc_status hc_diag_tile_map(int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_
   clear_error();
   if (!out_shape) return fail(HC_EINVAL, "null output pointer");
   if (d_kv <= 0 || n_tok <= 0 || n_layers <= 0 || n_layers > kMaxLayersPerLaunch)
-    return fail(HC_EINVAL, "d_kv > 0, n_tok > 0, 1 <= n_layers <= 8");
+    return fail(HC_EINVAL, "d_kv > 0, n_tok > 0, 1 <= n_layers <= 32");
   TileGrid g;
   const int slots = choose_tile_grid(2 * round_up(d_kv, kPartAlign) / kTileF, (n_tok + kTileT - 1) / kTileT, g);
   out_shape[0] = g.nf;

@@ -241,9 +241,9 @@ __host__ __device__ inline void split_range(int nm, int n, int s, int& m_begin, 
 // plan_split's figures give for the tiles, with the workspace traffic of the live token blocks only.
 // Below d_model 1024 the large tiles' workgroups take too short for a second order of sums to
 // be worth having: there every launch adds a token's channels up in the same order.
-// Measured, this kernel against the tiles: 16 tokens 10.2 / 24.8 us (d_model 4096, 8 heads),
-// 18.7 / 34.5 (32 heads), 29.3 / 41.7 (5120, 40 heads); 64 tokens 10.4 / 26.6, 23.6 / 36.6, 40.6 /
-// 43.9; 256 tokens 15.9 / 34.1, 61.3 / 47.7, 88.0 / 59.5.  Narrow K/V: 1700 tokens of 4096 channels
+// Measured, this kernel against the tiles, us per call back to back, the layers (600 MB of weights) in turn: 16
+// tokens 10.7 / 25.5 (d_model 4096, 8 heads), 15.8 / 34.8 (32 heads), 26.8 / 42.2 (5120, 40 heads); 64 tokens
+// 10.2 / 27.1, 21.7 / 36.9; 256 tokens of 4096, 8 heads 16.1 / 35.7.  Narrow K/V: 1700 tokens of 4096 channels
 // onto 128 features 24.4 / 32.8, 4000 tokens 47.8 / 39.8 (not taken), 9000 of 1024 channels 53.7 / 26.4 (not taken).
 constexpr int kSmallMinModel = 1024;
 constexpr float kSmallRoundUs = 3.f;
@@ -268,10 +268,10 @@ constexpr float kSmallRoundUs = 3.f;
 // takes 0.3 % (one layer) and 1.9 % (several) longer than the fastest kernel in the mean, and 22 are more than 4 %
 // slower than the large tiles; workgroups counted over the whole chip instead of its busiest part
 // made that 166 (20 layers of 4096 onto 2048, 179 tokens 136 us against 99; 8627 tokens of 7872 onto 128 108 against 65).
-// Measured, these tiles against the large ones (whole or split): one layer of 4096 onto 2048, 800 tokens
-// 25.5 / 44.0 us, 4000 tokens 62.9 / 90.9, 6000 tokens 98.4 / 99.6 (not taken); 5120 onto 10240, 300
-// tokens 52.8 / 62.9, 900 99.0 / 120, 1200 147 / 123 (not taken); 32 layers of 4096 onto 2048, 40
-// tokens 111 / 126, 256 tokens 181 / 147 (not taken).
+// Measured, these tiles against the large ones (whole or split), us per call back to back, the layers (600 MB of weights) in
+// turn: 4096 onto 2048, 800 tokens 28.2 / 44.2, 4000 tokens 66.4 / 93.8; 5120 onto 10240, 300 tokens
+// 58.2 / 70.1, 900 124.2 / 126.8 (99.4 / 125.0 with one layer's weights in the caches), 1200 147 / 123 (not
+// taken); 32 layers of 4096 onto 2048, 40 tokens 113 / 144, 256 tokens 181 / 147 (not taken).
 constexpr float kMidStepUs[6] = {0.f, 0.41f, 0.57f, 0.725f, 0.835f, 1.29f};
 constexpr float kMidSharedStepUs = 0.48f;                // nb = 1, two workgroups on a CU
 constexpr float kMidFixedUs = 2.5f, kMidBlockUs = 0.75f, kMidPromise = 1.09f;
@@ -352,7 +352,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
 // Arguments of one restoration launch (device pointers unless noted).
 struct RestoreArgs {
   const uint16_t* hidden;        // bf16 [n_tok, d_model]
-  const uint16_t* wpack;         // bf16 packed weight tiles [n_phys/256][d_model/32][256][32], gamma folded in
+  const uint16_t* wpack;         // bf16 packed weight tiles [n_phys/256][d_model/32][16 blocks][4 chunks][16 rows][8], gamma folded in
   const int32_t* positions;      // [n_tok] or nullptr: position = pos_base + row
   const int32_t* cu_seqlens;     // [n_seq + 1] or nullptr (single context)
   const int32_t* block_tables;   // [n_seq][max_blocks]
