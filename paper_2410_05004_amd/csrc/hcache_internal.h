@@ -272,7 +272,7 @@ constexpr float kSmallRoundUs = 3.f;
 // turn: 4096 onto 2048, 800 tokens 28.2 / 44.2, 4000 tokens 66.4 / 93.8; 5120 onto 10240, 300 tokens
 // 58.2 / 70.1, 900 124.2 / 126.8 (99.4 / 125.0 with one layer's weights in the caches), 1200 147 / 123 (not
 // taken); 32 layers of 4096 onto 2048, 40 tokens 113 / 144, 256 tokens 181 / 147 (not taken).
-constexpr float kMidStepUs[6] = {0.f, 0.41f, 0.57f, 0.725f, 0.835f, 1.29f};
+constexpr float kMidStepUs[6] = {0.f, 0.41f, 0.57f, 0.725f, 0.87f, 1.29f};
 constexpr float kMidSharedStepUs = 0.48f;                // nb = 1, two workgroups on a CU
 constexpr float kMidFixedUs = 2.5f, kMidBlockUs = 0.75f, kMidPromise = 1.09f;
 constexpr float kTileStepUs = 1.09f, kTileStepBusyUs = 0.45f, kTileNextRounds = 0.91f, kTileFixedUs = 4.7f;

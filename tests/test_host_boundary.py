@@ -465,6 +465,8 @@ int main() {
 # Measured on MI355X, weights not lately read: (d_model, d_kv, tokens, layers in the call or 0 for a single-layer call,
 # LayerNorm, us on the 256 x 256 tiles (whole or split), [us on tiles of 128 rows x 64, 128, .. 320 tokens])
 ROWS128_TIMES = [
+    (4096, 1024, 11650, 0, 0, 196.5, [298.8, 263.7, 231.2, 214.6, 301.4]),
+    (4096, 1024, 12286, 0, 0, 205.5, [307.3, 267.5, 233.4, 214.5, 304.6]),
     (7872, 64, 8627, 0, 0, 65.36, [107.52, 79.21, 97.24, 117.34, 183.67]),
     (5312, 2304, 217, 6, 1, 112.76, [154.88, 151.82, 183.74, 165.87, 233.05]),
     (192, 192, 13144, 0, 1, 14.6, [14.24, 16.59, 21.33, 14.81, 16.77]),
