@@ -410,10 +410,13 @@ hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
  * in hc_restore_kv (n_layers = 0; the ragged batch and the restores from a store likewise) or the first launch
  * of hc_restore_kv_layers over n_layers layers, under split mode `mode`.
  * out_route[4] = { kernel: 0 the tiles of 256 features x 256 tokens, 1 the few-token kernel, 2 the tiles of
- * 128 rows; its token blocks per workgroup (of 16 tokens for kernel 1, of 64 for kernel 2, 0 for kernel 0);
+ * 128 rows; its token blocks per workgroup (of 16 tokens for kernel 1, of 64, rounded up, for kernel 2, 0 for kernel 0);
  * workgroups per split tile (1: not split); layers in the launch }. */
 hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
                         int32_t mode, int32_t* out_route);
+/* The tile of the same launch: out_tile[3] = { packed weight rows, tokens per workgroup, waves that only load }. */
+hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
+                       int32_t mode, int32_t* out_tile);
 
 /* ---- measurement hooks -------------------------------------------------------------
  * Average duration in milliseconds of the restoration kernel launches (one per layer, or

@@ -16,6 +16,7 @@ from .binding import (  # noqa: F401
     validate_desc,
     static_stage_bytes,
     diag_mfma_duty,
+    diag_tile,
     diag_tile_map,
     diag_split_plan,
     diag_route,

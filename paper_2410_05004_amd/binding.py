@@ -90,6 +90,7 @@ def _load():
         "hc_saver_save_layer_host": (i32, [vp, i32, vp, i32, vp]),
         "hc_saver_flush": (i32, [vp]),
         "hc_diag_route": (i32, [i32, i32, i32, i32, i32, i32, p(i32)]),
+        "hc_diag_tile": (i32, [i32, i32, i32, i32, i32, i32, p(i32)]),
         "hc_diag_tile_map": (i32, [i32, i32, i32, p(i32), p(i32), C.c_int64]),
         "hc_diag_mfma_duty": (i32, [C.c_double, C.c_double, i32, C.c_double, i32, i32, p(C.c_double)]),
         "hc_timing_begin": (i32, [vp]),
@@ -111,7 +112,7 @@ EXPORTED = ("hc_last_error hc_version hc_validate_desc hc_create hc_destroy hc_s
             "hc_saver_flush hc_partition_layers hc_gather_kv hc_scatter_kv "
             "hc_restore_context_mixed hc_set_layer_weights_affine hc_saver_save_layer_deferred "
             "hc_saver_fence hc_restore_kv_layers hc_restore_contexts hc_timing_end_stats "
-            "hc_restore_context_static hc_static_stage_bytes hc_poison_staging hc_diag_mfma_duty hc_diag_tile_map hc_set_split hc_diag_split_plan hc_diag_route").split()
+            "hc_restore_context_static hc_static_stage_bytes hc_poison_staging hc_diag_mfma_duty hc_diag_tile_map hc_set_split hc_diag_split_plan hc_diag_route hc_diag_tile").split()
 
 
 def _check(status):
@@ -137,6 +138,13 @@ def diag_route(d_model, d_kv, n_tok, n_layers=0, norm_kind=HC_NORM_RMS, mode=1):
     out = (C.c_int32 * 4)()
     _check(lib.hc_diag_route(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out))
     return (("tiles", "few", "rows128")[out[0]], out[1], out[2], out[3])
+
+
+def diag_tile(d_model, d_kv, n_tok, n_layers=0, norm_kind=HC_NORM_RMS, mode=1):
+    """hc_diag_tile: (packed weight rows, tokens, waves that only load) of a workgroup of the launch."""
+    out = (C.c_int32 * 3)()
+    _check(lib.hc_diag_tile(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out))
+    return tuple(out)
 
 
 def diag_tile_map(d_kv, n_tok, n_layers=1):

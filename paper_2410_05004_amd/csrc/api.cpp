@@ -491,10 +491,11 @@ hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
   return HC_OK;
 }
 
-hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
-                        int32_t mode, int32_t* out_route) {
+// The route of the launch hc_diag_route and hc_diag_tile describe, and its layers.
+static hc_status diag_launch(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
+                             int32_t mode, const void* out, Route& route, int& layers) {
   clear_error();
-  if (!out_route) return fail(HC_EINVAL, "null output pointer");
+  if (!out) return fail(HC_EINVAL, "null output pointer");
   if (d_model <= 0 || d_model % 64 != 0 || d_kv <= 0 || d_kv % 64 != 0 || n_tok <= 0 || n_layers < 0)
     return fail(HC_EINVAL, "bad shape");
   if (norm_kind != HC_NORM_RMS && norm_kind != HC_NORM_LAYER) return fail(HC_EINVAL, "bad norm_kind");
@@ -508,12 +509,35 @@ hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_
   float ws;                                              // stands for a context's workspace: not read
   set_split_rule(a, mode, &ws, n_layers > 0);
   const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT, n_layers);
-  const int n = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
-  const Route route = restore_route(a, n);
-  out_route[0] = route.kind;
-  out_route[1] = route.nb;
+  layers = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
+  route = restore_route(a, layers);
+  return HC_OK;
+}
+
+hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
+                        int32_t mode, int32_t* out_route) {
+  Route route;
+  int layers;
+  const hc_status s = diag_launch(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out_route, route, layers);
+  if (s != HC_OK) return s;
+  const bool stream = route.kind == Route::kStream;       // tiles of 128 rows too
+  out_route[0] = stream ? Route::kMid : route.kind;
+  out_route[1] = stream ? (route.nb + 1) / 2 : route.nb;
   out_route[2] = route.split ? route.split_plan.n_split : 1;
-  out_route[3] = n;
+  out_route[3] = layers;
+  return HC_OK;
+}
+
+hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
+                       int32_t mode, int32_t* out_tile) {
+  Route route;
+  int layers;
+  const hc_status s = diag_launch(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out_tile, route, layers);
+  if (s != HC_OK) return s;
+  static const int kTile[4][2] = {{kTileF, kTileT}, {32, 16}, {128, 64}, {128, 32}};   // rows; tokens, or tokens per block
+  out_tile[0] = kTile[route.kind][0];
+  out_tile[1] = kTile[route.kind][1] * (route.kind == Route::kTiles ? 1 : route.nb);
+  out_tile[2] = route.kind == Route::kStream ? 4 : 0;
   return HC_OK;
 }
 

@@ -280,9 +280,43 @@ constexpr float kSplitPrice = 1.06f;
 constexpr float kWeightsUsPerByte = 1.f / 7.7e6f;
 constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token kernel and split tiles read them
 
+// Tiles of 128 rows x 32 nb tokens with loader waves (restore_stream.inc), nb = 2 .. 6; the same sums in the same order again.
+// Cost, fitted on the times of nb = 2 .. 6 at 2000 random single-layer shapes (d_model 1024 .. 8192, 192 .. 8192
+// K/V features, 16 .. 16384 tokens; each with the weights from memory and from the caches, geometric mean; 8 %) and
+// 2000 of two to eight layers (9 %): rounds as above, of step us per 64 channels, growing with nb and with how many of the
+// CUs are busy (the clock falls), `more` of it for every further round of several layers, whose CUs have lost step; the
+// hypotenuse of that and the operands' time from memory (the hidden states count 2.4 times: several XCDs fetch them).
+// Over those shapes, time under this rule against the one without these tiles (weights from memory where three copies of
+// the layer do not fit the caches): single layers 0.944 in the geometric mean (0.931 if every choice were the fastest), 6 of
+// 2000 more than 4 % slower, 610 faster; several layers (485 of 2000 take these tiles) 0.925, 5 and 465.
+// Where the lines lie:
+//  * d_model above 1024: below, up to 16 supersteps, a launch is mostly prologue, epilogue and its issue, and these tiles gain
+//    a microsecond or two (700 shapes: 0.92 of the time in the median up to 256 channels, 0.87 at 512 .. 1024, 0.82 above);
+//    the tiles of 64 n tokens stay.
+//  * a single layer of up to two rounds: beyond, the gain is gone with the CUs' step (1601 tokens of 5120 onto 10240, 2.8
+//    rounds of 192-token tiles: 187 us against 162 in split 256 x 256 tiles).
+//  * two to four layers, where the loop takes longer than the operands (kStreamOverMemory): weights that stream from
+//    memory come in faster through eight loading waves, or two workgroups on a CU (20 layers of 8192 channels onto 2048, 43 tokens:
+//    160 us here, 144 with 64-token tiles), and in longer launches the CUs are out of step for most of the time (best of these
+//    tiles over the earlier choice, median: 0.75 at two to four layers of 3000 channels and more, 0.90 .. 1.02 at five to
+//    twelve, 1.00 .. 1.05 beyond).  Weights whose token tiles fall into different rounds are read again
+//    (kStreamWeightsAgain): 2 layers of 5120 onto 10240, 228 tokens: 101 us in tiles of 96 tokens, 80 in those of 256.
+//  * 192 K/V features or more: what the fit covers.
+//  * against the few-token kernel a quarter more (kFewOverStream), which its own estimate is too high by for wide K/V (41
+//    tokens of 5120 onto 10240: 27.4 us, these tiles 32.6).
+constexpr int kStreamMinModel = 1024, kStreamMinKv = 192, kStreamMostLayers = 4;
+struct StreamCost {
+  float step, block, busy, busy_block, norm_block;        // us per 64 channels and round: idle chip, all CUs busy, LayerNorm
+  float more, round, round_block, call, hidden_times, us_per_byte, promise;
+};
+constexpr StreamCost kStreamCost[2] = {                   // one layer, several
+    {0.163f, 0.0364f, -0.0161f, 0.0362f, 0.0052f, 0.f, 2.1f, 0.47f, 1.3f, 2.3f, 1.f / 6.86e6f, 1.09f},
+    {0.049f, 0.0477f, 0.0643f, 0.0177f, 0.0056f, 0.0378f, 1.9f, 0.32f, 5.4f, 2.4f, 1.f / 6.46e6f, 1.04f}};
+constexpr float kStreamMostRounds = 2.f, kStreamOverMemory = 1.f, kStreamWeightsAgain = 0.8f, kFewOverStream = 1.25f;
+
 struct Route {
-  enum Kind { kTiles, kSmall, kMid } kind = kTiles;
-  int nb = 0;              // token blocks per workgroup of the other two
+  enum Kind { kTiles, kSmall, kMid, kStream } kind = kTiles;
+  int nb = 0;              // tokens per workgroup of the others: in 16s (kSmall), 64s (kMid), 32s (kStream)
   bool split = false;      // kTiles: the launch is split by
   SplitPlan split_plan{};
   TileGrid grid{};         // kTiles: of the tiles computed whole
@@ -331,6 +365,30 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     if (t < best) { best = t; route.kind = Route::kMid; route.nb = b; }
   }
 
+  if (d_model > kStreamMinModel && d_kv >= kStreamMinKv && n_layers <= kStreamMostLayers) {
+    const StreamCost& k = kStreamCost[n_layers > 1];
+    const float bytes_us = (weights + k.hidden_times * 2.f * (float)n_tok * d_model) * n_layers * k.us_per_byte;
+    float stream = best;
+    int nb = 0;
+    for (int b = 2; b <= 6; ++b) {
+      float loop_us;
+      auto cost = [&](float wgs) {                         // workgroups per CU of the busiest part
+        const float rounds = ceilf(wgs);
+        const float step_us = k.step + k.block * b + (k.busy + k.busy_block * b) * (wgs / rounds) + (layer_norm ? k.norm_block * b : 0.f);
+        loop_us = rounds * (step_us * nm * (1.f + k.more * fminf(rounds - 1.f, 9.f)) + k.round + k.round_block * b) + k.call;
+        const float again_us = n_layers > 1 && rounds > 1.f && n_tok > 32 * b ? kStreamWeightsAgain * weights * n_layers * k.us_per_byte : 0.f;
+        return k.promise * hypotf(loop_us, bytes_us + again_us);
+      };
+      const int nt_b = (n_tok + 32 * b - 1) / (32 * b);
+      if (cost((float)groups * nt_b * n_layers / kChipCUs) >= stream) continue;   // even if the parts were equally busy
+      const float wgs = launch_load(groups_pad, nt_b, groups, n_layers);
+      if (n_layers == 1 && wgs > kStreamMostRounds) continue;
+      const float t = cost(wgs);
+      if (t < stream) { stream = t; nb = n_layers == 1 || bytes_us < kStreamOverMemory * loop_us ? b : 0; }
+    }
+    if (nb) { best = stream; route.kind = Route::kStream; route.nb = nb; }
+  }
+
   if (n_layers == 1 && free_order && d_model >= kSmallMinModel) {
     const int units = (2 * d_kv / kPairGroup + 7) / 8 * 2;   // 32-row units of the busiest XCD
     int nb = 0;
@@ -343,7 +401,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
       if (b == 1 || t < stream_us) { stream_us = t; nb = b; }
     }
     const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
-    if (t < best) { best = t; route.kind = Route::kSmall; route.nb = nb; }
+    if (t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
   if (route.kind != Route::kTiles) route.split = false;
   return route;
@@ -432,6 +490,8 @@ struct LayerBatch {
 hipError_t launch_restore(const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers, hipStream_t stream);
 // Tiles of 128 packed rows x 64 nb tokens (nb 1..5), one launch; `batch` as in launch_restore.
 hipError_t launch_restore_mid(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
+// Tiles of 128 packed rows x 32 nb tokens with loader waves (nb 2..6), one launch; `batch` as in launch_restore.
+hipError_t launch_restore_stream(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
 hipError_t launch_restore_small(const RestoreArgs& a, int nb, hipStream_t stream);
 // The kernel a launch of n_layers layers of `a` takes.  A context that asks for split launches gets the
 // 256 x 256 tiles.
@@ -460,6 +520,7 @@ hipError_t launch_pack_affine(const uint16_t* wkv, const uint16_t* gamma, const 
 hipError_t launch_rope_table(float2* table, int max_position, int head_dim, double theta,
                              hipStream_t stream);
 hipError_t configure_mid();
+hipError_t configure_stream();
 hipError_t configure_kernels();   // one-time function attributes (dynamic LDS size)
 // Measurement only: chip-wide matrix-op rate (TFLOP/s, as if all 256 CUs were busy) inside
 // the busy windows of a duty-cycled burst pattern; allocates and frees its own buffers and

@@ -1,6 +1,9 @@
-// What the three restoration kernels share on the device: vector types, bf16 rounding of a pair, and the
-// lookup of a token row's position and context.
+// What the restoration kernels share on the device: vector types, bf16 rounding of a pair, the rotation of a
+// pair, and the lookup of a token row's position and context.
 #pragma once
+
+#include <type_traits>
+#include <utility>
 
 #include "hcache_internal.h"
 
@@ -17,6 +20,20 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   f32x2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));   // round to nearest even
 }
+
+// Rotation of a RoPE pair (a, b) by (cos, sin).  The roundings are spelt out: kernels that promise the same bits may
+// not leave it to the compiler which of the two products is fused.
+__device__ __forceinline__ void rotate_pair(float& a, float& b, float c, float s) {
+  const float ra = __builtin_fmaf(a, c, -(b * s));
+  b = __builtin_fmaf(b, c, a * s);
+  a = ra;
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
 // Position and context of token row t (of a batch without positions, every context starts at pos_base).
 __device__ __forceinline__ void token_place(const RestoreArgs& a, int t, int& pos, int& seq) {

@@ -1,5 +1,7 @@
-// LayerNorm + projection bias instantiations of the restoration kernel.
+// LayerNorm + projection bias instantiations of the restoration kernel; the translation unit of the tiles of
+// 128 rows with loader waves.
 #include "restore_kernel.inc"
+#include "restore_stream.inc"
 
 namespace hc {
 

@@ -1,0 +1,101 @@
+"""Tiles of 128 rows with loader waves: bit for bit the 256 x 256 tiles' results and error flags, at the edges of the
+tiles, for every tile width, norm, rotation and head size, layer by layer, together and as a ragged batch."""
+import numpy as np
+import pytest
+
+import gpu_harness as gh
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hc():
+    import paper_2410_05004_amd as m
+    return m
+
+
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm,alone,together", [
+    # alone, together: tokens per workgroup of a single-layer call and of the call over all layers (None: another kernel)
+    (1088, 3, 64, 1, 2, 0, "rms", None, 64),           # one token; padded K/V parts; 17 supersteps
+    (1152, 5, 64, 1025, 1, 1, "rms", 64, 64),          # one token in the last tile
+    (1152, 5, 64, 1025, 1, 0, "layer", 64, 64),
+    (1088, 3, 128, 321, 2, 2, "bias", None, 96),       # no rotation: no table rows
+    (1088, 17, 192, 257, 1, 0, "layer", 96, 96),       # pair groups that straddle the packed tile's halves
+    (1152, 43, 64, 385, 1, 1, "bias", 96, 96),         # one token in the fifth tile
+    (2112, 5, 64, 385, 3, 0, "layer", None, 128),
+    (1088, 17, 192, 385, 1, 1, "rms", 128, 128),
+    (1088, 3, 192, 257, 3, 0, "bias", None, 160),
+    (1152, 32, 64, 1025, 1, 2, "layer", 160, 160),
+    (1152, 8, 192, 801, 4, 0, "rms", 96, 160),         # one token in the sixth tile
+    (1152, 3, 192, 321, 3, 1, "rms", None, 192),
+    (1088, 43, 64, 801, 1, 0, "layer", 192, 192),
+])
+def test_stream_tiles_equal_whole_tiles(hc, d_model, n_kv, hd, n_tok, layers, style, norm, alone, together):
+    import torch
+    layer_norm = norm == "layer"
+    tile = lambda n: hc.diag_tile(d_model, n_kv * hd, n_tok, n, layer_norm)
+    assert alone is None or tile(0) == (128, alone, 4)
+    assert layers == 1 or tile(layers) == (128, together, 4)
+    torch.manual_seed(d_model * 7919 + n_tok)
+    rows, B, offset = 2 * n_kv * hd, 16, 40
+    desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                        max_position=offset + n_tok, rope_style=style, norm_kind=int(layer_norm))
+    ctx, s = hc.Context(desc), gh.stream_handle()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    n_blocks = (offset + n_tok + B - 1) // B
+    num_pages = n_blocks + 3
+    keep, pools, xs = [], [], []
+    for l in range(layers):
+        w, gain = torch.randn((rows, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+        shift = 0.1 * torch.randn(d_model, **bf) if layer_norm else None
+        bias = 0.1 * torch.randn(rows, **bf) if norm != "rms" else None
+        keep += [w, gain, shift, bias]
+        if norm == "rms":
+            ctx.set_layer_weights(l, w, gain, s)
+        else:
+            ctx.set_layer_weights_affine(l, w, gain, shift, bias, s)
+        pools.append(gh.new_pool(num_pages, B, n_kv, hd))
+        ctx.set_kv_pool(l, pools[l], num_pages)
+        xs.append(torch.randn((n_tok, d_model), **bf) + 0.25)
+    # positions in no order, one past max_position; the last page is not one of the pool
+    pos = (offset + torch.randperm(n_tok, device="cuda")).to(torch.int32)
+    table = torch.randperm(num_pages, device="cuda")[:n_blocks].to(torch.int32)
+    if n_tok > 2:
+        pos[n_tok // 2] = offset + n_tok
+        table[-1] = num_pages
+    cu = torch.tensor([0, n_tok // 3, n_tok], dtype=torch.int32, device="cuda")
+    tables = torch.stack([table, table])
+
+    def outcome(mode, call):
+        ctx.set_split(mode)
+        for p in pools:
+            p.view(torch.int16).fill_(np.array(gh.SENTINEL, dtype=np.uint16).view(np.int16).item())
+        call()
+        return ctx.poll_device_error(s), [gh.pool_bits(p) for p in pools]
+
+    def whole():
+        for l in range(layers):
+            gh.restore_whole_tiles(ctx, l, xs[l], pos, n_tok, table, n_blocks, s)
+
+    def single():
+        for l in range(layers):
+            ctx.restore_kv(l, xs[l], pos, n_tok, table, n_blocks, s)
+
+    def ragged():
+        for l in range(layers):
+            ctx.restore_kv_ragged(l, xs[l], pos, n_tok, cu, 2, tables, n_blocks, s)
+
+    def several():
+        ctx.restore_kv_layers(0, xs, pos, n_tok, table, n_blocks, s)
+
+    flags, want = outcome(2, whole)
+    assert flags == (hc.HC_DEV_BAD_POSITION | hc.HC_DEV_BAD_PAGE if n_tok > 2 else 0)
+    assert all(0 < (b != gh.SENTINEL).sum() <= n_tok * rows for b in want)
+    calls = ([single, ragged] if alone else []) + ([several] if layers > 1 else [])
+    for call in calls:
+        for _ in range(2):
+            got_flags, got = outcome(1, call)
+            assert got_flags == flags
+            for g, b in zip(got, want):
+                assert np.array_equal(g, b)
+    ctx.destroy()
