@@ -414,7 +414,8 @@ hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
  * workgroups per split tile (1: not split); layers in the launch }. */
 hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
                         int32_t mode, int32_t* out_route);
-/* The tile of the same launch: out_tile[3] = { packed weight rows, tokens per workgroup, waves that only load }. */
+/* The tile of the same launch: out_tile[4] = { packed weight rows, tokens per workgroup, waves that only load, 1 if a
+ * launch of its own works LayerNorm's sums out ahead (not while the stream is being captured) }. */
 hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
                        int32_t mode, int32_t* out_tile);
 

@@ -141,8 +141,9 @@ def diag_route(d_model, d_kv, n_tok, n_layers=0, norm_kind=HC_NORM_RMS, mode=1):
 
 
 def diag_tile(d_model, d_kv, n_tok, n_layers=0, norm_kind=HC_NORM_RMS, mode=1):
-    """hc_diag_tile: (packed weight rows, tokens, waves that only load) of a workgroup of the launch."""
-    out = (C.c_int32 * 3)()
+    """hc_diag_tile: (packed weight rows, tokens, waves that only load) of a workgroup of the launch, and 1 if LayerNorm's
+    sums are worked out ahead of it."""
+    out = (C.c_int32 * 4)()
     _check(lib.hc_diag_tile(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out))
     return tuple(out)
 

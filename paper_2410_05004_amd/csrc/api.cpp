@@ -98,6 +98,25 @@ static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, LayerBatch* bat
     HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used], stream));
   }
   const Route route = restore_route(a, n_layers);
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (route.sums_ahead) HC_HIP(hipStreamIsCapturing(stream, &capturing));
+  if (route.sums_ahead && capturing == hipStreamCaptureStatusNone) {   // a captured launch must not wait for an event of the outside
+    std::lock_guard<std::mutex> lock(ctx->sums_mutex);
+    const int slot = ctx->sums_next;
+    ctx->sums_next = (slot + 1) % kSumsSlots;
+    float2* sums = ctx->sums + slot * kSumsTokens;
+    RestoreArgs b = a;
+    b.token_sums = sums;
+    HC_HIP(hipStreamWaitEvent(stream, ctx->sums_done[slot], 0));
+    HC_HIP(launch_token_sums(a, batch, n_layers, sums, stream));
+    HC_HIP(launch_restore(b, route, batch, n_layers, stream));
+    HC_HIP(hipEventRecord(ctx->sums_done[slot], stream));
+    if (timed) {
+      HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used + 1], stream));
+      ctx->ev_used += 2;
+    }
+    return HC_OK;
+  }
   // the workspace is one per context: a split launch waits for the one before it, whatever its stream
   if (route.split) HC_HIP(hipStreamWaitEvent(stream, ctx->split_done, 0));
   HC_HIP(launch_restore(a, route, batch, n_layers, stream));
@@ -227,8 +246,11 @@ hc_status hc_create(const hc_model_desc* desc, hc_ctx** out) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->err_dev), 256);
   if (e == hipSuccess) e = hipMemset(ctx->err_dev, 0, 256);
   if (e == hipSuccess)
-    e = hipMalloc(reinterpret_cast<void**>(&ctx->split_ws), (size_t)kSplitMaxSlots * kSplitSlotFloats * sizeof(float));
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->split_ws), (size_t)kSplitMaxSlots * kSplitSlotFloats * sizeof(float) + kSumsSlots * kSumsTokens * sizeof(float2));
+  if (e == hipSuccess) ctx->sums = reinterpret_cast<float2*>(ctx->split_ws + (size_t)kSplitMaxSlots * kSplitSlotFloats);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->split_done, hipEventDisableTiming);
+  for (hipEvent_t& ev : ctx->sums_done)
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
   if (e == hipSuccess && rotary)
     e = launch_rope_table(ctx->rope, desc->max_position, desc->head_dim, (double)desc->rope_theta,
                           nullptr);
@@ -239,6 +261,7 @@ hc_status hc_create(const hc_model_desc* desc, hc_ctx** out) {
     if (ctx->err_dev) (void)hipFree(ctx->err_dev);
     if (ctx->split_ws) (void)hipFree(ctx->split_ws);
     if (ctx->split_done) (void)hipEventDestroy(ctx->split_done);
+    for (hipEvent_t ev : ctx->sums_done) if (ev) (void)hipEventDestroy(ev);
     delete ctx;
     return st;
   }
@@ -258,6 +281,7 @@ hc_status hc_destroy(hc_ctx* ctx) {
   if (ctx->err_dev) (void)hipFree(ctx->err_dev);
   if (ctx->split_ws) (void)hipFree(ctx->split_ws);
   if (ctx->split_done) (void)hipEventDestroy(ctx->split_done);
+  for (hipEvent_t ev : ctx->sums_done) if (ev) (void)hipEventDestroy(ev);
   if (ctx->copy2) (void)hipStreamDestroy(ctx->copy2);
   for (int i = 0; i < 2; ++i) {
     if (ctx->stage[i]) (void)hipFree(ctx->stage[i]);
@@ -538,6 +562,7 @@ hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_l
   out_tile[0] = kTile[route.kind][0];
   out_tile[1] = kTile[route.kind][1] * (route.kind == Route::kTiles ? 1 : route.nb);
   out_tile[2] = route.kind == Route::kStream ? 4 : 0;
+  out_tile[3] = route.sums_ahead ? 1 : 0;
   return HC_OK;
 }
 

@@ -132,6 +132,55 @@ hipError_t launch_pack_affine(const uint16_t* wkv, const uint16_t* gamma, const 
   return hipGetLastError();
 }
 
+// ---- tokens' sums ahead of the tiles ---------------------------------------------------
+// Sum of squares and plain sum of every token row, by the very matrix ops, in the order, that the tiles use (restore_kernel.inc),
+// so that results do not depend on where the sums come from.  A wave takes 16 tokens; lane l16 of quarter q4 reads
+// 16 bytes of row l16, 64 contiguous bytes per row and step, sixteen steps in flight.
+// Bound: memory: 8 x 2048 rows of 7168 channels (235 MB) in some 55 us.
+__global__ __launch_bounds__(256) void token_sums_kernel(const LayerBatch mb, int n_tok, int d_model, float2* __restrict__ out) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, q4 = lane >> 4;
+  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
+  if (t0 >= n_tok) return;
+  const int t = t0 + l16;
+  const bf16x8* x = reinterpret_cast<const bf16x8*>(mb.e[blockIdx.y].hidden + (size_t)(t < n_tok ? t : n_tok - 1) * d_model) + q4;
+  const int nk = d_model / kTileK;                        // even
+  f32x4 gram = {0.f, 0.f, 0.f, 0.f}, lin = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  constexpr int kDeep = 8;
+  bf16x8 f[2][kDeep];
+  auto load = [&](int u, int k0) __attribute__((always_inline)) {   // steps past the end: the last one again, not added
+#pragma unroll
+    for (int i = 0; i < kDeep; ++i) f[u][i] = x[(k0 + i < nk ? k0 + i : nk - 1) * 4];
+  };
+  auto add = [&](int u, int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kDeep; ++i)
+      if (k0 + i < nk) {
+        gram = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[u][i], f[u][i], gram, 0, 0, 0);
+        lin = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, f[u][i], lin, 0, 0, 0);
+      }
+  };
+  load(0, 0);
+  for (int k = 0; k < nk; k += 2 * kDeep) {
+    load(1, k + kDeep);
+    add(0, k);
+    load(0, k + 2 * kDeep);
+    add(1, k + kDeep);
+  }
+  const int v = l16 & 3;
+  const float sq = v == 0 ? gram[0] : v == 1 ? gram[1] : v == 2 ? gram[2] : gram[3];
+  if (q4 == (l16 >> 2) && t < n_tok) out[(size_t)blockIdx.y * n_tok + t] = make_float2(sq, lin[0]);
+}
+
+hipError_t launch_token_sums(const RestoreArgs& a, const LayerBatch* batch, int n_layers, float2* out, hipStream_t stream) {
+  LayerBatch one;
+  if (!batch) one.e[0].hidden = a.hidden;
+  hipLaunchKernelGGL(token_sums_kernel, dim3((a.n_tok + 63) / 64, n_layers), dim3(256), 0, stream, batch ? *batch : one, a.n_tok, a.d_model, out);
+  return hipGetLastError();
+}
+
 // ---- RoPE table -----------------------------------------------------------------------
 // table[p][i] = (cos, sin)(p * theta^(-2i/hd)), evaluated in fp64 and rounded once to fp32:
 // an fp32 product p * inv_freq would already be off by ~2e-3 rad at position 32768.

@@ -314,9 +314,29 @@ constexpr StreamCost kStreamCost[2] = {                   // one layer, several
     {0.049f, 0.0477f, 0.0643f, 0.0177f, 0.0056f, 0.0378f, 1.9f, 0.32f, 5.4f, 2.4f, 1.f / 6.46e6f, 1.04f}};
 constexpr float kStreamMostRounds = 2.f, kStreamOverMemory = 1.f, kStreamWeightsAgain = 0.8f, kFewOverStream = 1.25f;
 
+// LayerNorm's sums ahead of the 256 x 256 tiles (token_sums_kernel).  Every feature tile of a token tile works the same
+// sums out, by 4 of its 36 matrix ops, and at the chip's power limit they cost as much as any other: 0.16 us per 64
+// channels and round.  A pass over the hidden states ahead of the launch takes their time from memory (4.5 TB/s) and
+// some 6 us.  Measured, sums in the tiles / ahead: eight layers of 2048 tokens, 7168 channels onto 14336 features 2515 / 2330 us (4.3
+// times the pass in estimated savings), one layer of 4096 tokens 672 / 644 (3.3 times), of 2048 tokens 337 / 337 (2.5
+// times: a last round that is three quarters full gets no shorter): the line lies at 2.8.  RMSNorm's sums are half as many
+// ops: 8192 and 20000 tokens of 5120 onto 10240 took the same either way (603 / 602, 1530 / 1532 us).
+// The sums go to one of kSumsSlots slots of a context, in turn, so that launches on different streams seldom wait for
+// each other; a launch that does not fit a slot, or is being captured (it would have to wait for an event from
+// outside the capture), works them out in its tiles, with the same results bit for bit.
+constexpr int kSumsSlots = 4;
+constexpr size_t kSumsTokens = 262144;                    // token rows (of all layers of a launch) per slot
+constexpr float kSumsSaveUs = 0.16f, kSumsUsPerByte = 1.f / 4.5e6f, kSumsCallUs = 6.f, kSumsTimes = 2.8f;
+inline bool sums_pay_ahead(int nf, int nt, int nm, int n_tok, int n_layers) {
+  if ((size_t)n_tok * n_layers > kSumsTokens) return false;
+  const float save = (float)nf * nt * n_layers / kChipCUs * nm * kSumsSaveUs;
+  return save > kSumsTimes * ((float)n_tok * n_layers * nm * 128.f * kSumsUsPerByte + kSumsCallUs);
+}
+
 struct Route {
   enum Kind { kTiles, kSmall, kMid, kStream } kind = kTiles;
   int nb = 0;              // tokens per workgroup of the others: in 16s (kSmall), 64s (kMid), 32s (kStream)
+  bool sums_ahead = false; // kTiles: LayerNorm's sums ahead of the tiles
   bool split = false;      // kTiles: the launch is split by
   SplitPlan split_plan{};
   TileGrid grid{};         // kTiles: of the tiles computed whole
@@ -404,6 +424,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     if (t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
   if (route.kind != Route::kTiles) route.split = false;
+  if (layer_norm && route.kind == Route::kTiles && !route.split) route.sums_ahead = sums_pay_ahead(nf, nt, nm, n_tok, n_layers);
   return route;
 }
 
@@ -433,6 +454,7 @@ struct RestoreArgs {
   int32_t mode;                  // 0 RMSNorm, 1 RMSNorm + bias, 2 LayerNorm + bias
   float inv_d;                   // 1 / d_model
   float eps;
+  const float2* token_sums;      // [n_layers][n_tok] sums of squares and plain sums worked out ahead, or nullptr: in the tiles
   float* split_ws;               // workspace of the split launch, or nullptr: never split (host side only)
   int32_t split_force;           // split whenever the shape allows it, whatever the cost model says (host side only)
 };
@@ -509,6 +531,8 @@ inline void set_split_rule(RestoreArgs& a, int split_mode, float* split_ws, bool
   a.split_ws = !several && split_mode ? split_ws : nullptr;
   a.split_force = split_mode == 2;
 }
+// The tokens' sums of squares and plain sums of n_layers layers (`batch`, or a.hidden) into `out` [n_layers][n_tok].
+hipError_t launch_token_sums(const RestoreArgs& a, const LayerBatch* batch, int n_layers, float2* out, hipStream_t stream);
 hipError_t launch_pack_weights(const uint16_t* wkv, const uint16_t* gamma, uint16_t* wpack,
                                int d_model, int d_kv, int head_dim, int rope_style,
                                hipStream_t stream);
@@ -612,6 +636,12 @@ struct hc_ctx {
   // another stream waits for it
   float* split_ws = nullptr;
   hipEvent_t split_done = nullptr;
+  // slots of the tokens' sums worked out ahead of a launch (behind the split workspace), used in turn, each guarded by an
+  // event recorded behind its last reader
+  float2* sums = nullptr;
+  hipEvent_t sums_done[hc::kSumsSlots] = {};
+  int sums_next = 0;
+  std::mutex sums_mutex;
   int split_mode = 1;                     // 0 = never split, 1 = when plan_split's cost model says so, 2 = whenever possible
   // segment tables of the gather loader: pinned host memory the kernel reads directly; two of
   // them, used alternately, each guarded by an event recorded after its last reader

@@ -13,7 +13,7 @@ hipError_t launch_mode0(const RestoreArgs& a, const TileGrid& g, unsigned grid, 
 }
 hipError_t configure_mode0() { return configure_mode<0>(); }
 
-// Function attributes are a device's, not a context's: set once per device (74 kernels, some 80 us).
+// Function attributes are a device's, not a context's: set once per device (80 kernels, some 90 us).
 hipError_t configure_kernels() {
   static std::mutex mutex;
   static std::set<int> done;

@@ -1,0 +1,76 @@
+"""LayerNorm's sums worked out ahead of the 256 x 256 tiles: bit for bit the results of the sums in the tiles, in calls in a
+row that use more slots than there are, on two streams, and under capture, where the tiles work them out."""
+import numpy as np
+import pytest
+
+import gpu_harness as gh
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_model,n_kv,n_tok,layers,style", [
+    (2048, 64, 8190, 1, 2),        # 15 tokens of the last 16-token block, no rotation
+    (2048, 64, 4097, 2, 0),        # one token in the last tile and block
+    (2112, 64, 4097, 2, 1),        # 66 steps: the unrolled loop of the sums ends inside its last round
+])
+def test_sums_ahead_equal_sums_in_the_tiles(d_model, n_kv, n_tok, layers, style):
+    import torch
+    import paper_2410_05004_amd as hc
+    hd, B = 128, 16
+    assert hc.diag_tile(d_model, n_kv * hd, n_tok, layers if layers > 1 else 0, hc.HC_NORM_LAYER) == (256, 256, 0, 1)
+    torch.manual_seed(n_tok + d_model)
+    desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                        max_position=n_tok, rope_style=style, norm_kind=1)
+    ctx, s = hc.Context(desc), gh.stream_handle()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    n_blocks = -(-n_tok // B)
+    pos = torch.arange(n_tok, dtype=torch.int32, device="cuda")
+    table = torch.randperm(n_blocks + 2, device="cuda")[:n_blocks].to(torch.int32)
+    xs, pools = [], []
+    for l in range(layers):
+        w, gain, shift = torch.randn((2 * n_kv * hd, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf), 0.1 * torch.randn(d_model, **bf)
+        ctx.set_layer_weights_affine(l, w, gain, shift, None, s)
+        torch.cuda.synchronize()
+        xs.append(torch.randn((n_tok, d_model), **bf) + 0.25)
+        pools.append(torch.zeros((n_blocks + 2, 2, B, n_kv, hd), **bf))
+        ctx.set_kv_pool(l, pools[l], n_blocks + 2)
+
+    def call(stream):
+        if layers == 1:
+            ctx.restore_kv(0, xs[0], pos, n_tok, table, n_blocks, stream)
+        else:
+            ctx.restore_kv_layers(0, xs, pos, n_tok, table, n_blocks, stream)
+
+    for l in range(layers):
+        gh.restore_whole_tiles(ctx, l, xs[l], pos, n_tok, table, n_blocks, s)
+    torch.cuda.synchronize()
+    want = [p.clone() for p in pools]
+    ctx.set_split(1)
+
+    def check():
+        torch.cuda.synchronize()
+        for p, v in zip(pools, want):
+            assert torch.equal(p.view(torch.int16), v.view(torch.int16))
+            p.zero_()
+        torch.cuda.synchronize()
+
+    for p in pools:
+        p.zero_()
+    for _ in range(6):
+        call(s)
+    check()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        call(s)
+        call(side.cuda_stream)
+    check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        graph.replay()
+        check()
+        call(s)
+        check()
+    assert ctx.poll_device_error(s) == 0
+    ctx.destroy()

@@ -34,8 +34,8 @@ def test_stream_tiles_equal_whole_tiles(hc, d_model, n_kv, hd, n_tok, layers, st
     import torch
     layer_norm = norm == "layer"
     tile = lambda n: hc.diag_tile(d_model, n_kv * hd, n_tok, n, layer_norm)
-    assert alone is None or tile(0) == (128, alone, 4)
-    assert layers == 1 or tile(layers) == (128, together, 4)
+    assert alone is None or tile(0) == (128, alone, 4, 0)
+    assert layers == 1 or tile(layers) == (128, together, 4, 0)
     torch.manual_seed(d_model * 7919 + n_tok)
     rows, B, offset = 2 * n_kv * hd, 16, 40
     desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
