@@ -409,8 +409,8 @@ hc_status hc_diag_split_plan(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
 /* Host-side view of the kernel a restoration launch takes (no device work): a layer of d_model, d_kv and n_tok
  * in hc_restore_kv (n_layers = 0; the ragged batch and the restores from a store likewise) or the first launch
  * of hc_restore_kv_layers over n_layers layers, under split mode `mode`.
- * out_route[4] = { kernel: 0 the tiles of 256 features x 256 tokens, 1 the few-token kernel, 2 the tiles of
- * 128 rows; its token blocks per workgroup (of 16 tokens for kernel 1, of 64, rounded up, for kernel 2, 0 for kernel 0);
+ * out_route[4] = { kernel: 0 the tiles of 256 features x 256 tokens, 1 the few-token kernel, 2 tiles of
+ * other sizes (hc_diag_tile); its token blocks per workgroup (of 16 tokens for kernel 1, of 64, rounded up, for kernel 2, 0 for kernel 0);
  * workgroups per split tile (1: not split); layers in the launch }. */
 hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_layers, int32_t norm_kind,
                         int32_t mode, int32_t* out_route);

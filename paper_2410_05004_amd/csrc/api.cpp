@@ -86,7 +86,7 @@ static int layer_mode(const hc_ctx* ctx, const hc_layer_state& L) {
 }
 
 // One timed (when timing is on) launch.
-static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, LayerBatch* batch, int n_layers,
+static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers,
                               hipStream_t stream) {
   const bool timed = ctx->timing && ctx->ev_used + 2 <= 8192;
   if (timed) {
@@ -97,7 +97,6 @@ static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, LayerBatch* bat
     }
     HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used], stream));
   }
-  const Route route = restore_route(a, n_layers);
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (route.sums_ahead) HC_HIP(hipStreamIsCapturing(stream, &capturing));
   if (route.sums_ahead && capturing == hipStreamCaptureStatusNone) {   // a captured launch must not wait for an event of the outside
@@ -144,7 +143,7 @@ hc_status restore_layer(hc_ctx* ctx, int32_t layer, const void* d_hidden,
   a.pool = L.pool;
   a.num_pages = L.num_pages;
   set_split_rule(a, ctx->split_mode, ctx->split_ws, false);
-  return timed_launch(ctx, a, nullptr, 1, stream);
+  return timed_launch(ctx, a, restore_route(a, 1), nullptr, 1, stream);
 }
 
 hc_status restore_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
@@ -160,7 +159,9 @@ hc_status restore_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
   }
   RestoreArgs a = shared_args(ctx, d_positions, pos_base, n_tok, nullptr, 1, d_block_table, n_blocks);
   set_split_rule(a, ctx->split_mode, ctx->split_ws, true);
-  const int per_launch = layers_per_launch(2 * ctx->d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT, n_layers);
+  a.mode = layer_mode(ctx, ctx->layers[layer_begin]);
+  Route route;
+  const int per_launch = plan_layers(a, n_layers, route);
   int i = 0;
   while (i < n_layers) {
     // one launch per run of layers with the same kernel mode, at most per_launch of them
@@ -174,8 +175,10 @@ hc_status restore_layers(hc_ctx* ctx, int32_t layer_begin, int32_t n_layers,
                               L.num_pages};
       ++n;
     }
+    // the first launch's plan holds for those of as many layers and the same norm
+    const bool as_first = n == per_launch && (mode == 2) == (a.mode == 2);
     a.mode = mode;
-    hc_status r = timed_launch(ctx, a, &batch, n, stream);
+    hc_status r = timed_launch(ctx, a, as_first ? route : restore_route(a, n), &batch, n, stream);
     if (r != HC_OK) return r;
     i += n;
   }
@@ -532,9 +535,9 @@ static hc_status diag_launch(int32_t d_model, int32_t d_kv, int32_t n_tok, int32
   a.mode = norm_kind == HC_NORM_LAYER ? 2 : 0;
   float ws;                                              // stands for a context's workspace: not read
   set_split_rule(a, mode, &ws, n_layers > 0);
-  const int per_launch = layers_per_launch(2 * a.d_kv_pad / kTileF, (n_tok + kTileT - 1) / kTileT, n_layers);
-  layers = n_layers == 0 ? 1 : std::min(n_layers, per_launch);
-  route = restore_route(a, layers);
+  layers = 1;
+  if (n_layers == 0) route = restore_route(a, 1);
+  else               layers = plan_layers(a, n_layers, route);
   return HC_OK;
 }
 
@@ -544,9 +547,9 @@ hc_status hc_diag_route(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_
   int layers;
   const hc_status s = diag_launch(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out_route, route, layers);
   if (s != HC_OK) return s;
-  const bool stream = route.kind == Route::kStream;       // tiles of 128 rows too
-  out_route[0] = stream ? Route::kMid : route.kind;
-  out_route[1] = stream ? (route.nb + 1) / 2 : route.nb;
+  const bool in_32s = route.kind == Route::kStream || route.kind == Route::kWide;   // hc_diag_tile tells these from kMid
+  out_route[0] = in_32s ? Route::kMid : route.kind;
+  out_route[1] = in_32s ? (route.nb + 1) / 2 : route.nb;
   out_route[2] = route.split ? route.split_plan.n_split : 1;
   out_route[3] = layers;
   return HC_OK;
@@ -558,7 +561,7 @@ hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_l
   int layers;
   const hc_status s = diag_launch(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out_tile, route, layers);
   if (s != HC_OK) return s;
-  static const int kTile[4][2] = {{kTileF, kTileT}, {32, 16}, {128, 64}, {128, 32}};   // rows; tokens, or tokens per block
+  static const int kTile[5][2] = {{kTileF, kTileT}, {32, 16}, {128, 64}, {128, 32}, {256, 32}};   // rows; tokens, or tokens per block
   out_tile[0] = kTile[route.kind][0];
   out_tile[1] = kTile[route.kind][1] * (route.kind == Route::kTiles ? 1 : route.nb);
   out_tile[2] = route.kind == Route::kStream ? 4 : 0;

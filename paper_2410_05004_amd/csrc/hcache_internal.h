@@ -333,9 +333,31 @@ inline bool sums_pay_ahead(int nf, int nt, int nm, int n_tok, int n_layers) {
   return save > kSumsTimes * ((float)n_tok * n_layers * nm * 128.f * kSumsUsPerByte + kSumsCallUs);
 }
 
+// Tiles of 256 rows x 288 or 320 tokens (restore_wide.inc); the same sums in the same order again.  Estimate: rounds as above, of
+// 1.34 (288 tokens) or 1.5 us per 64 channels, 0.4 more as the CUs fill up, and 9; the hypotenuse of that and the operands'
+// time from memory (4.8 TB/s).  The other estimates are good to 9 % or so, so these tiles have to promise that.  Of the 2000
+// single-layer shapes they take 60, of the 2000 of several layers 66: 0.92 and 0.77 of the time in the geometric mean, none
+// more than 2 % slower (each against the same kernels' times on its own box).  LayerNorm, whose plain sums would need a
+// register more per block, and d_model below 2048, where nothing was measured, stay with the others.
+constexpr int kWideMinModel = 2048;
+constexpr float kWidePromise = 1.09f;
+inline float wide_us(int d_kv, int d_model, int n_tok, int n_layers, int& nb) {
+  const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF;
+  const float bytes_us = (4.f * d_kv * d_model + 2.f * n_tok * d_model) * n_layers * (1.f / 4.8e6f);
+  float best = 0.f;
+  for (int b = 9; b <= 10; ++b) {
+    const float load = launch_load(nf, (n_tok + 32 * b - 1) / (32 * b), nf, n_layers), rounds = ceilf(load);
+    const float loop_us = rounds * (((b == 9 ? 1.34f : 1.5f) + 0.4f * (load / rounds)) * (d_model / (2 * kTileK)) + 9.f);
+    const float t = kWidePromise * hypotf(loop_us, bytes_us);
+    if (b == 9 || t < best) { best = t; nb = b; }
+  }
+  return best;
+}
+
 struct Route {
-  enum Kind { kTiles, kSmall, kMid, kStream } kind = kTiles;
-  int nb = 0;              // tokens per workgroup of the others: in 16s (kSmall), 64s (kMid), 32s (kStream)
+  enum Kind { kTiles, kSmall, kMid, kStream, kWide } kind = kTiles;
+  int nb = 0;              // tokens per workgroup of the others: in 16s (kSmall), 64s (kMid), 32s (kStream, kWide)
+  float us = 0.f;          // what the launch is estimated to take
   bool sums_ahead = false; // kTiles: LayerNorm's sums ahead of the tiles
   bool split = false;      // kTiles: the launch is split by
   SplitPlan split_plan{};
@@ -423,6 +445,12 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
     if (t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
+  if (d_model >= kWideMinModel && !layer_norm) {
+    int nb = 0;
+    const float t = wide_us(d_kv, d_model, n_tok, n_layers, nb);
+    if (t < best) { best = t; route.kind = Route::kWide; route.nb = nb; }
+  }
+  route.us = best;
   if (route.kind != Route::kTiles) route.split = false;
   if (layer_norm && route.kind == Route::kTiles && !route.split) route.sums_ahead = sums_pay_ahead(nf, nt, nm, n_tok, n_layers);
   return route;
@@ -501,6 +529,14 @@ inline int layers_per_launch(int nf, int nt, int n_layers) {
   }
   return best;
 }
+// Layers per launch on the tiles of 288 or 320 tokens: as many as fill one round of the chip.
+inline int wide_layers_per_launch(int d_kv, int n_tok, int nb, int n_layers) {
+  const int tiles = 2 * round_up(d_kv, kPartAlign) / kTileF * ((n_tok + 32 * nb - 1) / (32 * nb));
+  int n = kChipCUs / tiles;
+  if (n > kMaxLayersPerLaunch) n = kMaxLayersPerLaunch;
+  if (n > n_layers) n = n_layers;
+  return n < 8 ? 8 : n;
+}
 struct LayerBatch {
   LayerEntry e[kMaxLayersPerLaunch];
   int32_t slots_per_layer;     // workgroups per layer (a multiple of 8); set by launch_restore
@@ -514,6 +550,8 @@ hipError_t launch_restore(const RestoreArgs& a, const Route& route, LayerBatch* 
 hipError_t launch_restore_mid(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
 // Tiles of 128 packed rows x 32 nb tokens with loader waves (nb 2..6), one launch; `batch` as in launch_restore.
 hipError_t launch_restore_stream(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
+// Tiles of 256 packed rows x 32 nb tokens (nb 9 or 10; not LayerNorm), one launch; `batch` as in launch_restore.
+hipError_t launch_restore_wide(const RestoreArgs& a, int nb, LayerBatch* batch, int n_layers, hipStream_t stream);
 hipError_t launch_restore_small(const RestoreArgs& a, int nb, hipStream_t stream);
 // The kernel a launch of n_layers layers of `a` takes.  A context that asks for split launches gets the
 // 256 x 256 tiles.
@@ -524,6 +562,25 @@ inline Route restore_route(const RestoreArgs& a, int n_layers) {
     r.split = plan_split(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, a.d_model / (2 * kTileK), true, r.split_plan, r.grid);
   r.split_plan.ws = a.split_ws;
   return r;
+}
+// Layers in the first launch of a call over n_layers layers of `a` (layers_per_launch), and its route; or more of them on the tiles
+// of 288 or 320 tokens where the whole call is estimated to take less that way (launches x estimate of one).
+inline int plan_layers(const RestoreArgs& a, int n_layers, Route& route) {
+  const int per = layers_per_launch(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, n_layers);
+  const int n = per < n_layers ? per : n_layers;
+  route = restore_route(a, n);
+  if (a.split_force || a.mode == 2 || a.d_model < kWideMinModel || n == n_layers) return n;
+  int nb = 0;
+  wide_us(a.d_kv, a.d_model, a.n_tok, n, nb);
+  const int n_wide = wide_layers_per_launch(a.d_kv, a.n_tok, nb, n_layers);
+  if (n_wide <= n) return n;
+  const float us = wide_us(a.d_kv, a.d_model, a.n_tok, n_wide, nb);
+  if (us * ((n_layers + n_wide - 1) / n_wide) >= route.us * ((n_layers + n - 1) / n)) return n;
+  route = Route();
+  route.kind = Route::kWide;
+  route.nb = nb;
+  route.us = us;
+  return n_wide;
 }
 // What a context's split mode asks of a launch: `several` layers in one launch never split, but they take
 // the 256 x 256 tiles too when split launches are asked for.
@@ -545,6 +602,7 @@ hipError_t launch_rope_table(float2* table, int max_position, int head_dim, doub
                              hipStream_t stream);
 hipError_t configure_mid();
 hipError_t configure_stream();
+hipError_t configure_wide();
 hipError_t configure_kernels();   // one-time function attributes (dynamic LDS size)
 // Measurement only: chip-wide matrix-op rate (TFLOP/s, as if all 256 CUs were busy) inside
 // the busy windows of a duty-cycled burst pattern; allocates and frees its own buffers and

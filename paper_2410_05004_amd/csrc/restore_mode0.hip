@@ -13,7 +13,7 @@ hipError_t launch_mode0(const RestoreArgs& a, const TileGrid& g, unsigned grid, 
 }
 hipError_t configure_mode0() { return configure_mode<0>(); }
 
-// Function attributes are a device's, not a context's: set once per device (80 kernels, some 90 us).
+// Function attributes are a device's, not a context's: set once per device (84 kernels, some 90 us).
 hipError_t configure_kernels() {
   static std::mutex mutex;
   static std::set<int> done;
@@ -27,6 +27,7 @@ hipError_t configure_kernels() {
   if (e == hipSuccess) e = configure_mode2();
   if (e == hipSuccess) e = configure_mid();
   if (e == hipSuccess) e = configure_stream();
+  if (e == hipSuccess) e = configure_wide();
   if (e == hipSuccess) done.insert(dev);
   return e;
 }
@@ -34,6 +35,7 @@ hipError_t configure_kernels() {
 hipError_t launch_restore(const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers, hipStream_t stream) {
   if (route.kind == Route::kMid) return launch_restore_mid(a, route.nb, batch, n_layers, stream);
   if (route.kind == Route::kStream) return launch_restore_stream(a, route.nb, batch, n_layers, stream);
+  if (route.kind == Route::kWide) return launch_restore_wide(a, route.nb, batch, n_layers, stream);
   if (route.kind == Route::kSmall) return launch_restore_small(a, route.nb, stream);
   TileGrid g = route.grid;
   const SplitPlan* use_split = route.split ? &route.split_plan : nullptr;

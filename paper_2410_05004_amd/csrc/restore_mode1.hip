@@ -1,7 +1,8 @@
 // RMSNorm + projection bias instantiations of the restoration kernel; the translation unit of the tiles
-// of 128 rows.
+// of 128 rows and of those of 288 and 320 tokens.
 #include "restore_kernel.inc"
 #include "restore_mid.inc"
+#include "restore_wide.inc"
 
 namespace hc {
 

@@ -1,4 +1,4 @@
-"""Tiles of 128 rows with loader waves: bit for bit the 256 x 256 tiles' results and error flags, at the edges of the
+"""Tiles of 128 rows with loader waves, and tiles of 288 and 320 tokens: bit for bit the 256 x 256 tiles' results and error flags, at the edges of the
 tiles, for every tile width, norm, rotation and head size, layer by layer, together and as a ragged batch."""
 import numpy as np
 import pytest
@@ -12,6 +12,16 @@ pytestmark = pytest.mark.gpu
 def hc():
     import paper_2410_05004_amd as m
     return m
+
+
+WIDE = [                                               # tiles of 256 rows x 288 or 320 tokens
+    (2048, 3, 192, 257, 20, 0, "rms", None, 288),      # padded K/V parts, pair groups that straddle the heads
+    (2112, 5, 64, 1153, 20, 1, "bias", None, 288),     # one token in the last tile; 66 steps: the ring ends elsewhere
+    (2048, 3, 192, 289, 20, 2, "bias", None, 320),     # one token in the last block but one; no rotation
+    (2112, 3, 192, 320, 20, 1, "rms", None, 320),      # a full tile
+    (2112, 40, 128, 1601, 1, 0, "rms", 288, 288),
+    (2048, 64, 128, 1153, 1, 1, "bias", 320, 320),
+]
 
 
 @pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm,alone,together", [
@@ -29,13 +39,13 @@ def hc():
     (1152, 8, 192, 801, 4, 0, "rms", 96, 160),         # one token in the sixth tile
     (1152, 3, 192, 321, 3, 1, "rms", None, 192),
     (1088, 43, 64, 801, 1, 0, "layer", 192, 192),
-])
+] + WIDE)
 def test_stream_tiles_equal_whole_tiles(hc, d_model, n_kv, hd, n_tok, layers, style, norm, alone, together):
     import torch
     layer_norm = norm == "layer"
     tile = lambda n: hc.diag_tile(d_model, n_kv * hd, n_tok, n, layer_norm)
-    assert alone is None or tile(0) == (128, alone, 4, 0)
-    assert layers == 1 or tile(layers) == (128, together, 4, 0)
+    assert alone is None or tile(0) == ((256, alone, 0, 0) if alone > 192 else (128, alone, 4, 0))
+    assert layers == 1 or tile(layers) == ((256, together, 0, 0) if together > 192 else (128, together, 4, 0))
     torch.manual_seed(d_model * 7919 + n_tok)
     rows, B, offset = 2 * n_kv * hd, 16, 40
     desc = gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
