@@ -445,7 +445,8 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
     if (t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
-  if (d_model >= kWideMinModel && !layer_norm) {
+  // One round of 288 tokens is the least that wide_us answers; its two launch_loads are host time of every call.
+  if (d_model >= kWideMinModel && !layer_norm && kWidePromise * (1.34f * nm + 9.f) < best) {
     int nb = 0;
     const float t = wide_us(d_kv, d_model, n_tok, n_layers, nb);
     if (t < best) { best = t; route.kind = Route::kWide; route.nb = nb; }
