@@ -148,7 +148,7 @@ hc_status hc_restore_kv(hc_ctx* ctx, int32_t layer, const void* d_hidden,
  * bf16 [n_tok, d_model] of layer layer_begin + i; positions and block table are shared (one
  * context).  The layers go out in launches of up to 8 layers each (for short contexts, whose
  * layers have fewer than 32 tiles of 256 features x 256 tokens: up to as many layers as fill the 256
- * compute units once, at most 32), which removes the gaps between per-layer kernels and lets the
+ * compute units once, at most 32; likewise with tiles of 288 or 320 tokens where those are estimated to take less), which removes the gaps between per-layer kernels and lets the
  * compute units run out of step.
  * Per layer the result is hc_restore_kv's bit for bit under hc_set_split(ctx, 0); in the default mode a
  * single layer may go to a split launch or to the few-token kernel (see hc_set_split), which add a token's
@@ -388,7 +388,8 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * round with few tiles takes as long as a full one.  mode 1 (default): when a cost model says it
  * pays (a last round at most half full, d_model of about 2048 or more), the token tiles outside
  * the full rounds are computed by several workgroups each, every one over a contiguous share
- * of d_model, into an fp32 workspace the context owns (allocated by hc_create, 66 MiB), and a
+ * of d_model, into an fp32 workspace the context owns (allocated by hc_create, 66 MiB, with 8 MiB behind it for
+ * LayerNorm's sums of long launches), and a
  * second launch adds the shares up in a fixed order and finishes them (normalisation, RoPE,
  * scatter).  Results are deterministic and within the same tolerance, but not bit-identical to
  * an unsplit launch (fp32 summation order).  Split launches of one context are ordered after
@@ -398,8 +399,8 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * a kernel of its own when that is estimated faster than whole or split tiles (up to some 1500 to 2000 tokens
  * with one or two heads of 128, 500 with 8, 130 with 32, 30 to 60 with 56); its workgroups' waves share the
  * d_model loop, so the same holds for its results; it uses no workspace and one launch.  In modes 0 and 1 launches that whole tiles
- * fill badly (a short context, a device partly idle) go to tiles of 128 features x 64..320 tokens,
- * whose results are those of the unsplit 256 x 256 tiles bit for bit. */
+ * fill badly (a short context, a device partly idle, a last row of few tokens) go to tiles of 128 features x 64..320
+ * tokens or 256 features x 288 or 320 tokens, whose results are those of the unsplit 256 x 256 tiles bit for bit. */
 hc_status hc_set_split(hc_ctx* ctx, int32_t mode);
 /* Host-side view of the split of a layer of d_model, d_kv and n_tok under `mode` when it goes to the
  * 256 x 256 tiles (no device work): out_plan[8] = { 1 if split else 0, feature tiles, token tiles, token tiles
