@@ -462,6 +462,47 @@ int main() {
     assert out.returncode == 0, out.stdout
 
 
+def test_rows_of_tiles_with_loader_waves(tmp_path):
+    """tile_base_row and tile_row, as the kernel uses them: live rows are the tile's own, the others lie within the tokens, none is
+    read much more often than the rest, and byte offsets fit 32 bits (a tile of 192 rows alone allows d_model of 10 million)."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src = tmp_path / "rows.cpp"
+    src.write_text("""
+#include <cstdio>
+#include <vector>
+#include "hcache_internal.h"
+using namespace hc;
+int main() {
+  long bad = 0, n = 0;
+  for (int T = 64; T <= 192; T += 32)
+    for (int n_tok = 1; n_tok <= 3 * T + 1; ++n_tok)
+      for (int d : {1088, 7168, 1 << 22, (1 << 22) + 64, 10 << 20})
+        for (int t0 = 0; t0 < n_tok; t0 += T) {
+          const int base = tile_base_row(t0, n_tok, T, d), live = n_tok - t0 < T ? n_tok - t0 : T;
+          std::vector<int> reads(n_tok);
+          bad += base < 0;
+          for (int r = 0; r < T; ++r, ++n) {
+            const int off = tile_row(r, t0, base, n_tok), row = base + off;
+            if (off < 0 || row < 0 || row >= n_tok) { ++bad; continue; }
+            bad += r < live && row != t0 + r;
+            bad += (unsigned long long)off * d * 2 + 128 > 0xffffffffull;
+            bad += ++reads[row] > (t0 > 0 && d <= 1 << 22 ? 1 : (T + live - 1) / live);
+          }
+        }
+  std::printf("%ld of %ld\\n", bad, n);
+  return bad != 0;
+}
+""")
+    inc = [os.path.join(ROOT, "include"), os.path.join(ROOT, "paper_2410_05004_amd", "csrc")]
+    exe = tmp_path / "rows"
+    subprocess.run([hipcc, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-I", inc[0], "-I", inc[1],
+                    str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+
+
 # Measured on MI355X, weights not lately read: (d_model, d_kv, tokens, layers in the call or 0 for a single-layer call,
 # LayerNorm, us on the 256 x 256 tiles (whole or split), [us on tiles of 128 rows x 64, 128, .. 320 tokens])
 ROWS128_TIMES = [
