@@ -315,16 +315,17 @@ constexpr StreamCost kStreamCost[2] = {                   // one layer, several
 constexpr float kStreamMostRounds = 2.f, kStreamOverMemory = 1.f, kStreamWeightsAgain = 0.8f, kFewOverStream = 1.25f;
 
 // Rows of the hidden states that a tile with loader waves, T tokens at t0, reads: its own, and in the place of those past
-// the end each another one, never used: the same row of the tile before, whose workgroups bring it into the L2 at that time,
-// or in the only tile the live ones over again.  (The last row for all of them is one line of one L2 channel, asked for by every
-// workgroup of the tile in every superstep: 65 tokens of 7168 channels onto 14336 took 53.6 us, 128 tokens 38.3; now 37.4.)
+// the end, whose results nothing uses, its own over again, or where fewer than eight are left sixteen of the tile before.  The last
+// row for all of them is one line asked for up to T times by every workgroup of the tile in every superstep: 65 tokens of 7168
+// channels onto 14336 took 52.8 us, weights from the caches, and 128 tokens 38.7; now 39.8 (58.8 -> 55 with weights from memory).
+// Rows of the tile before for all of them are more lines to bring in: 37.6 and 61; tiles with eight live rows or more lost up to 8 % by it.
 // tile_row is relative to tile_base_row, which keeps byte offsets of up to two tiles within 32 bits.
 __host__ __device__ inline int tile_base_row(int t0, int n_tok, int T, int d_model) {
-  return t0 > 0 && n_tok - t0 < T && d_model <= 1 << 22 ? t0 - T : t0;
+  return t0 > 0 && n_tok - t0 < 8 && d_model <= 1 << 22 ? t0 - T : t0;
 }
 __host__ __device__ inline int tile_row(int r, int t0, int base_row, int n_tok) {
   const int live = n_tok - t0;
-  return r < live ? t0 - base_row + r : base_row < t0 ? r : r % live;
+  return r < live ? t0 - base_row + r : base_row < t0 ? r & 15 : r % live;
 }
 
 // LayerNorm's sums ahead of the 256 x 256 tiles (token_sums_kernel).  Every feature tile of a token tile works the same

@@ -482,13 +482,13 @@ int main() {
         for (int t0 = 0; t0 < n_tok; t0 += T) {
           const int base = tile_base_row(t0, n_tok, T, d), live = n_tok - t0 < T ? n_tok - t0 : T;
           std::vector<int> reads(n_tok);
-          bad += base < 0;
+          bad += base < 0 || (t0 > 0 && live < 8 && d <= 1 << 22) != (base < t0);
           for (int r = 0; r < T; ++r, ++n) {
             const int off = tile_row(r, t0, base, n_tok), row = base + off;
             if (off < 0 || row < 0 || row >= n_tok) { ++bad; continue; }
             bad += r < live && row != t0 + r;
             bad += (unsigned long long)off * d * 2 + 128 > 0xffffffffull;
-            bad += ++reads[row] > (t0 > 0 && d <= 1 << 22 ? 1 : (T + live - 1) / live);
+            bad += ++reads[row] > (base < t0 ? (T + 15) / 16 : (T + live - 1) / live);
           }
         }
   std::printf("%ld of %ld\\n", bad, n);
