@@ -348,3 +348,53 @@ def test_opt_style_ragged_and_streamed(hc):
         gh.compare_pool(gh.pool_bits(pools[l]), ora)
     ctx.destroy()
     store.destroy()
+
+
+@pytest.mark.parametrize("n_tok", [1, 15, 17, 63, 65, 129, 257, 300])
+@pytest.mark.parametrize("norm,style,hd", [("rms", 0, 64), ("bias", 1, 128), ("bias", 2, 64), ("layer", 0, 128), ("layer", 1, 64), ("layer", 2, 192)])
+def test_large_tiles_with_a_last_tile_of_few_tokens(hc, n_tok, norm, style, hd):
+    """256 x 256 tiles, whole and over several layers: the tokens of a partly filled tile come out bit for bit as in a full
+    one, wherever the end lies among the waves and token blocks, and nothing else of the pool is written."""
+    import torch
+    d_model, n_kv, full, B, layers = 192, 3, 512, 16, 2
+    torch.manual_seed(n_tok * 7 + hd)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    ctx, s = hc.Context(gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                                     max_position=full, rope_style=style, norm_kind=int(norm == "layer"))), gh.stream_handle()
+    rows, num_pages = 2 * n_kv * hd, full // B + 2
+    pos = torch.randperm(full, device="cuda").to(torch.int32)
+    table = torch.randperm(num_pages, device="cuda")[:full // B].to(torch.int32)
+    pools, xs, keep = [], [], []
+    for l in range(layers):
+        w, gain = torch.randn((rows, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+        shift = 0.1 * torch.randn(d_model, **bf) if norm == "layer" else None
+        bias = 0.1 * torch.randn(rows, **bf) if norm != "rms" else None
+        keep += [w, gain, shift, bias]
+        if norm == "rms":
+            ctx.set_layer_weights(l, w, gain, s)
+        else:
+            ctx.set_layer_weights_affine(l, w, gain, shift, bias, s)
+        pools.append(gh.new_pool(num_pages, B, n_kv, hd))
+        ctx.set_kv_pool(l, pools[l], num_pages)
+        xs.append(torch.randn((full, d_model), **bf) + 0.25)
+    ctx.set_split(2)                                       # large tiles; nothing splits at three supersteps
+    assert hc.diag_tile(d_model, n_kv * hd, n_tok, 0, int(norm == "layer"), 2)[:2] == (256, 256)
+
+    def outcome(n, together):
+        for p in pools:
+            p.view(torch.int16).fill_(np.array(gh.SENTINEL, dtype=np.uint16).view(np.int16).item())
+        if together:
+            ctx.restore_kv_layers(0, xs, pos, n, table, full // B, s)
+        else:
+            for l in range(layers):
+                ctx.restore_kv(l, xs[l], pos, n, table, full // B, s)
+        assert ctx.poll_device_error(s) == 0
+        return [gh.pool_bits(p) for p in pools]
+
+    want = outcome(full, True)
+    page, slot = table[pos[:n_tok].long() // B].cpu().numpy(), (pos[:n_tok] % B).cpu().numpy()
+    for together in (False, True):
+        for got, ref in zip(outcome(n_tok, together), want):
+            assert np.array_equal(got[page, :, slot], ref[page, :, slot])
+            assert (got != gh.SENTINEL).sum() == n_tok * rows
+    ctx.destroy()
