@@ -303,7 +303,8 @@ constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token ker
 //    (kStreamWeightsAgain): 2 layers of 5120 onto 10240, 228 tokens: 101 us in tiles of 96 tokens, 80 in those of 256.
 //  * 192 K/V features or more: what the fit covers.
 //  * against the few-token kernel a quarter more (kFewOverStream), which its own estimate is too high by for wide K/V (41
-//    tokens of 5120 onto 10240: 27.4 us, these tiles 32.6).
+//    tokens of 5120 onto 10240: 27.4 us, these tiles 32.6); not where the tiles of 64 n tokens or the large ones are estimated
+//    below it as well (995 tokens of 1664 onto 768: 15.9 us in the few-token kernel, 12.5 here).
 constexpr int kStreamMinModel = 1024, kStreamMinKv = 192, kStreamMostLayers = 4;
 struct StreamCost {
   float step, block, busy, busy_block, norm_block;        // us per 64 channels and round: idle chip, all CUs busy, LayerNorm
@@ -421,6 +422,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     if (t < best) { best = t; route.kind = Route::kMid; route.nb = b; }
   }
 
+  const float others = best;                               // the tiles above
   if (d_model > kStreamMinModel && d_kv >= kStreamMinKv && n_layers <= kStreamMostLayers) {
     const StreamCost& k = kStreamCost[n_layers > 1];
     const float bytes_us = (weights + k.hidden_times * 2.f * (float)n_tok * d_model) * n_layers * k.us_per_byte;
@@ -457,7 +459,7 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
       if (b == 1 || t < stream_us) { stream_us = t; nb = b; }
     }
     const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
-    if (t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
+    if (t < others && t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
   // One round of 288 tokens is the least that wide_us answers; its two launch_loads are host time of every call.
   if (d_model >= kWideMinModel && !layer_norm && kWidePromise * (1.34f * nm + 9.f) < best) {

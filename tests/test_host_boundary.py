@@ -397,6 +397,29 @@ def test_few_token_kernel_only_where_it_was_measured_faster(hc):
         assert hc.diag_route(d_model, d_kv, n_tok)[0] == "few"
 
 
+# Measured on MI355X: (d_model, d_kv, tokens, LayerNorm, {kernel: (us with the weights from memory, from the caches)}); "stream": tiles of
+# 64 tokens with loader waves, "rows": the best of the tiles of 128 rows x 64 n tokens
+FEW_OR_TILES_TIMES = [
+    (1664, 8064, 35, 0, dict(few=(19.92, 15.64), stream=(17.61, 11.76), rows=(20.46, 13.27))),
+    (1408, 1152, 322, 0, dict(few=(13.93, 12.75), stream=(9.97, 9.24), rows=(12.03, 11.19))),
+    (1344, 3264, 125, 0, dict(few=(15.4, 11.51), stream=(13.7, 8.8), rows=(14.53, 10.28))),
+    (1280, 256, 1607, 1, dict(few=(14.03, 13.58), stream=(10.05, 9.43), rows=(12.29, 11.19))),
+    (5376, 7808, 63, 0, dict(few=(44.54, 33.91), stream=(43.64, 28.19), rows=(46.06, 29.46))),
+    (1856, 6656, 64, 1, dict(few=(22.39, 16.12), stream=(20.45, 13.28), rows=(22.74, 14.92))),
+    (1920, 256, 2036, 0, dict(few=(18.75, 17.4), stream=(15.87, 12.79), rows=(17.19, 14.44))),
+]
+
+
+def test_few_token_kernel_only_where_no_tiles_are_estimated_faster(hc):
+    """Shapes whose tiles of 64 tokens, with and without loader waves, are both faster than the few-token kernel: the margin
+    that one of them gives it does not carry it past the other."""
+    for d_model, d_kv, n_tok, norm, us in FEW_OR_TILES_TIMES:
+        kernel = "few" if hc.diag_route(d_model, d_kv, n_tok, 0, norm)[0] == "few" else "stream" if hc.diag_tile(d_model, d_kv, n_tok, 0, norm)[2] else "rows"
+        where = (d_model, d_kv, n_tok, norm, kernel, us)
+        assert all(a <= 1.05 * b for k in us for a, b in zip(us[kernel], us[k])), where
+    assert hc.diag_route(5120, 5120, 41)[0] == "few"       # 27.4 us, 32.6 on tiles with loader waves
+
+
 # Measured on MI355X: (d_model, d_kv, tokens, layers, {layers in the first launch: us of the call}), 256 x 256 tiles
 LAYERS_PER_LAUNCH_TIMES = [
     (640, 2816, 239, 10, {8: 56.8, 10: 36.8}), (256, 2688, 173, 10, {8: 32.0, 10: 23.5}),
