@@ -301,6 +301,9 @@ constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token ker
 //    tiles over the earlier choice, median: 0.75 at two to four layers of 3000 channels and more, 0.90 .. 1.02 at five to
 //    twelve, 1.00 .. 1.05 beyond).  Weights whose token tiles fall into different rounds are read again
 //    (kStreamWeightsAgain): 2 layers of 5120 onto 10240, 228 tokens: 101 us in tiles of 96 tokens, 80 in those of 256.
+//    A second round whose weights are not in the last-level cache (kLastCacheBytes) waits for memory: 3 layers of 5120 onto 10240, 161
+//    tokens: 118 us here, 106 on the large tiles; of 1446 launches taken at two to four layers, 33 were more than 4 % slower than
+//    the tiles they displaced, 17 with a fifth more for those (kStreamColdRounds).
 //  * 192 K/V features or more: what the fit covers.
 //  * against the few-token kernel a quarter more (kFewOverStream), which its own estimate is too high by for wide K/V (41
 //    tokens of 5120 onto 10240: 27.4 us, these tiles 32.6); not where the tiles of 64 n tokens or the large ones are estimated
@@ -314,6 +317,26 @@ constexpr StreamCost kStreamCost[2] = {                   // one layer, several
     {0.163f, 0.0364f, -0.0161f, 0.0362f, 0.0052f, 0.f, 2.1f, 0.47f, 1.3f, 2.3f, 1.f / 6.86e6f, 1.09f},
     {0.049f, 0.0477f, 0.0643f, 0.0177f, 0.0056f, 0.0378f, 1.9f, 0.32f, 5.4f, 2.4f, 1.f / 6.46e6f, 1.04f}};
 constexpr float kStreamMostRounds = 2.f, kStreamOverMemory = 1.f, kStreamWeightsAgain = 0.8f, kFewOverStream = 1.25f;
+constexpr float kStreamColdRounds = 1.2f, kLastCacheBytes = 2.56e8f;
+
+// Least time of a launch of nf x nt tiles of 128 rows: that of filling the L2s (all layers' bytes).  Every super tile brings its rows of
+// the weights into its XCD's L2, but for those that an XCD works on at once and that lie in one column (k and k + 8 do where 8 is a
+// multiple of the columns), and the hidden states come into the L2 of each XCD that has a column.  6.6 TB/s and 3.5 us, fitted on the
+// tiles with loader waves of 9925 launches: those that this bounds were estimated 24 % too low without it and are 2 % with it
+// (7 % rms).  Super tiles of one token tile each, taken because no other shape fits the XCDs evenly, are the usual case: 853
+// tokens of 4224 channels onto 7168 in nine tiles of 96 tokens bring in the weights nine times, 545 MB: 86 us, 65 in tiles of 64 n
+// tokens.  Of 2411 single-layer shapes 94 go elsewhere by it, to 0.88 of the time, 3 of them more than 4 % slower.  No
+// estimate of a kernel, so no promise on top.  Up to 1024 channels nothing was measured against it.
+constexpr float kL2FillUsPerByte = 1.f / 6.6e6f, kL2FillUs = 3.5f;
+inline float l2_fill_us(int nf, int nt, float weights, float hidden, float out) {
+  TileGrid g;
+  choose_tile_grid(nf, nt, g);
+  const int gt_shift = g.g_shift - g.gf_shift, rows = (nt + (1 << gt_shift) - 1) >> gt_shift;
+  int at_once = (g.nsf * rows + 7) / 8;                    // super tiles that an XCD works on at once
+  if (at_once > 32 >> g.g_shift) at_once = 32 >> g.g_shift;
+  const int columns = 8 % g.nsf == 0 ? 1 : at_once < g.nsf ? at_once : g.nsf;   // of those
+  return (weights * rows * columns / at_once + hidden * (g.nsf < 8 ? g.nsf : 8) + out) * kL2FillUsPerByte + kL2FillUs;
+}
 
 // Rows of the hidden states that a tile with loader waves, T tokens at t0, reads: its own, and in the place of those past
 // the end, whose results nothing uses, its own over again, or where fewer than eight are left sixteen of the tile before.  The last
@@ -418,7 +441,8 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     if (b > 1 && cost((float)groups * nt_b * n_layers / kChipCUs) >= best) continue;   // even if the parts were equally busy
     const float wgs = launch_load(groups_pad, nt_b, groups, n_layers, b == 1);
     if (b == 1 && wgs > (n_layers > 1 ? 6.f : 2.f)) continue;
-    const float t = cost(wgs);
+    float t = cost(wgs);
+    if (t < best && nt_b > 1 && d_model > kStreamMinModel) t = fmaxf(t, l2_fill_us(groups_pad, nt_b, weights * n_layers, 2.f * d_model * n_tok * n_layers, 4.f * d_kv * n_tok * n_layers));
     if (t < best) { best = t; route.kind = Route::kMid; route.nb = b; }
   }
 
@@ -441,7 +465,9 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
       if (cost((float)groups * nt_b * n_layers / kChipCUs) >= stream) continue;   // even if the parts were equally busy
       const float wgs = launch_load(groups_pad, nt_b, groups, n_layers);
       if (n_layers == 1 && wgs > kStreamMostRounds) continue;
-      const float t = cost(wgs);
+      float t = cost(wgs);
+      if (n_layers > 1 && nt_b == 1 && wgs > 1.f && route.kind == Route::kTiles && weights * n_layers > kLastCacheBytes) t *= kStreamColdRounds;
+      if (t < stream && nt_b > 1) t = fmaxf(t, l2_fill_us(groups_pad, nt_b, weights * n_layers, 2.f * d_model * n_tok * n_layers, 4.f * d_kv * n_tok * n_layers));
       if (t < stream) { stream = t; nb = n_layers == 1 || bytes_us < kStreamOverMemory * loop_us ? b : 0; }
     }
     if (nb) { best = stream; route.kind = Route::kStream; route.nb = nb; }

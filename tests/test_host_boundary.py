@@ -567,3 +567,32 @@ def test_tiles_of_128_rows_only_where_they_were_measured_faster(hc):
         where = (d_model, d_kv, n_tok, n_layers, norm, kernel, blocks, us, tiles_us, rows_us)
         assert us <= 1.05 * tiles_us, where
         assert min(rows_us) > 0.7 * tiles_us or us <= 1.1 * min(rows_us), where
+
+
+# Measured on MI355X: (d_model, d_kv, tokens, layers in the call or 0, LayerNorm, {(rows, tokens, loader waves) of a tile: us}), a single
+# layer with the weights from memory, several over and over
+TILE_TIMES = [
+    (4224, 3584, 853, 0, 0, {(128, 96, 4): 86.8, (128, 256, 0): 66.9}),      # nine token tiles: the weights into the L2s nine times
+    (4864, 2816, 993, 0, 0, {(128, 96, 4): 97.7, (128, 256, 0): 81.4}),
+    (3072, 3328, 803, 0, 0, {(128, 96, 4): 63.2, (128, 256, 0): 51.4}),
+    (7872, 4608, 615, 0, 1, {(128, 96, 4): 155.5, (256, 256, 0): 129.4}),
+    (1728, 1344, 2182, 0, 0, {(128, 96, 4): 38.4, (128, 256, 0): 32.2}),
+    (5120, 5120, 346, 0, 1, {(128, 128, 4): 56.5, (128, 128, 0): 62.7}),     # both bound by that
+    (3136, 896, 3216, 0, 1, {(128, 192, 4): 44.5, (128, 192, 0): 51.7}),
+    (7168, 7168, 191, 4, 1, {(128, 192, 4): 220.5, (256, 256, 0): 191.5}),   # second rounds from memory
+    (5120, 5120, 173, 4, 0, {(128, 192, 4): 136.0, (256, 256, 0): 120.0}),
+    (5120, 5120, 161, 3, 0, {(128, 192, 4): 118.5, (256, 256, 0): 106.0}),
+    (5120, 5120, 120, 4, 0, {(128, 128, 4): 120.1, (128, 128, 0): 128.8}),
+    (4096, 1024, 2501, 0, 0, {(128, 160, 4): 48.1, (128, 192, 0): 54.4}),
+]
+
+
+def test_tiles_with_loader_waves_only_where_they_were_measured_faster(hc):
+    """The launch rule against measured times of tiles with and without loader waves and of the large ones: the tile
+    chosen takes at most 1.05 of the fastest of those measured."""
+    for d_model, d_kv, n_tok, n_layers, norm, us in TILE_TIMES:
+        tile = hc.diag_tile(d_model, d_kv, n_tok, n_layers, norm)[:3]
+        best = min(us.values())
+        assert tile not in us or us[tile] <= 1.05 * best, (d_model, d_kv, n_tok, n_layers, norm, tile, us)
+        # a tile that is not in the row is no tile with loader waves, which are measured at each of their widths
+        assert tile in us or tile[2] == 0, (d_model, d_kv, n_tok, n_layers, norm, tile, us)
