@@ -371,25 +371,27 @@ inline bool sums_pay_ahead(int nf, int nt, int nm, int n_tok, int n_layers) {
   return save > kSumsTimes * ((float)n_tok * n_layers * nm * 128.f * kSumsUsPerByte + kSumsCallUs);
 }
 
-// Tiles of 256 rows x 288 or 320 tokens (restore_wide.inc); the same sums in the same order again.  Estimate: rounds as above, of
-// 1.34 (288 tokens) or 1.5 us per 64 channels, 0.4 more as the CUs fill up, and 9; the hypotenuse of that and the operands'
-// time from memory (4.8 TB/s).  The other estimates are good to 9 % or so, so these tiles have to promise that.  Of the 2000
-// single-layer shapes they take 60, of the 2000 of several layers 66: 0.92 and 0.77 of the time in the geometric mean, none
-// more than 2 % slower (each against the same kernels' times on its own box).  LayerNorm, whose plain sums would need a
-// register more per block, and d_model below 2048, where nothing was measured, stay with the others.
+// Tiles of 256 rows x 288 or 320 tokens (restore_wide.inc); the same sums in the same order again.  Estimate: rounds as above, of so
+// much per 64 channels, more as the CUs fill up, and a fixed part; the hypotenuse of that and the operands' time from memory.  One layer: fitted on
+// 2000 shapes (5 % over 187 launches).  Several: on 3114 launches of 2048 channels and more (5 %; the one layer's figures were 6 % too high
+// in the mean, 10 % where a launch leaves CUs idle, which hid that one launch of 20 layers of 300 tokens, 4096 channels onto 2048, takes
+// 136 us and 16 + 4 on the 256-token tiles 162).  The other estimates are good to 9 % or so, so against them
+// these tiles have to promise that, 12 % with several layers; against a whole call of other launches, whose errors even out, 4 %.  Of 5328
+// measured calls of several layers 58 go elsewhere by this than with the one layer's figures for all, to 0.86 of the time, none
+// more than 4 % slower (at 9 % four of 87 are).  LayerNorm, whose plain sums would need a register more per block, and d_model below
+// 2048, where nothing was measured, stay with the others.
 constexpr int kWideMinModel = 2048;
-constexpr float kWidePromise = 1.09f;
-inline float wide_us(int d_kv, int d_model, int n_tok, int n_layers, int& nb) {
+constexpr float kWideCallPromise = 1.04f;
+struct WideCost { float step[2], busy, round, hidden_times, us_per_byte, promise; };   // step: 288, 320 tokens
+constexpr WideCost kWideCost[2] = {                       // one layer, several
+    {{1.34f, 1.5f}, 0.4f, 9.f, 1.f, 1.f / 4.8e6f, 1.09f}, {{1.09f, 1.27f}, 0.45f, 16.6f, 2.1f, 1.f / 6.06e6f, 1.12f}};
+inline float wide_us(int d_kv, int d_model, int n_tok, int n_layers, int nb) {
+  const WideCost& k = kWideCost[n_layers > 1];
   const int nf = 2 * round_up(d_kv, kPartAlign) / kTileF;
-  const float bytes_us = (4.f * d_kv * d_model + 2.f * n_tok * d_model) * n_layers * (1.f / 4.8e6f);
-  float best = 0.f;
-  for (int b = 9; b <= 10; ++b) {
-    const float load = launch_load(nf, (n_tok + 32 * b - 1) / (32 * b), nf, n_layers), rounds = ceilf(load);
-    const float loop_us = rounds * (((b == 9 ? 1.34f : 1.5f) + 0.4f * (load / rounds)) * (d_model / (2 * kTileK)) + 9.f);
-    const float t = kWidePromise * hypotf(loop_us, bytes_us);
-    if (b == 9 || t < best) { best = t; nb = b; }
-  }
-  return best;
+  const float bytes_us = (4.f * d_kv * d_model + k.hidden_times * 2.f * n_tok * d_model) * n_layers * k.us_per_byte;
+  const float load = launch_load(nf, (n_tok + 32 * nb - 1) / (32 * nb), nf, n_layers), rounds = ceilf(load);
+  const float loop_us = rounds * ((k.step[nb - 9] + k.busy * (load / rounds)) * (d_model / (2 * kTileK)) + k.round);
+  return hypotf(loop_us, bytes_us);
 }
 
 struct Route {
@@ -487,11 +489,13 @@ inline Route plan_route(int d_kv, int d_model, int n_tok, int n_layers, bool lay
     const float t = 3.5f + sqrtf(stream_us * stream_us + few_weights_us * few_weights_us);
     if (t < others && t < best * (route.kind == Route::kStream ? kFewOverStream : 1.f)) { best = t; route.kind = Route::kSmall; route.nb = nb; }
   }
-  // One round of 288 tokens is the least that wide_us answers; its two launch_loads are host time of every call.
-  if (d_model >= kWideMinModel && !layer_norm && kWidePromise * (1.34f * nm + 9.f) < best) {
-    int nb = 0;
-    const float t = wide_us(d_kv, d_model, n_tok, n_layers, nb);
-    if (t < best) { best = t; route.kind = Route::kWide; route.nb = nb; }
+  // One round of 288 tokens is the least that wide_us answers; its launch_load is host time of every call.
+  const WideCost& wide = kWideCost[n_layers > 1];
+  if (d_model >= kWideMinModel && !layer_norm && wide.promise * (wide.step[0] * nm + wide.round) < best) {
+    for (int b = 9; b <= 10; ++b) {
+      const float t = wide.promise * wide_us(d_kv, d_model, n_tok, n_layers, b);
+      if (t < best) { best = t; route.kind = Route::kWide; route.nb = b; }
+    }
   }
   route.us = best;
   if (route.kind != Route::kTiles) route.split = false;
@@ -607,23 +611,33 @@ inline Route restore_route(const RestoreArgs& a, int n_layers) {
   return r;
 }
 // Layers in the first launch of a call over n_layers layers of `a` (layers_per_launch), and its route; or more of them on the tiles
-// of 288 or 320 tokens where the whole call is estimated to take less that way (launches x estimate of one).
+// of 288 or 320 tokens where the whole call is estimated to take less that way.  A call is its full launches and the last one, of
+// the layers that are left, which goes its own way: 33 layers of 257 tokens of 8192 channels onto 2048 take 337 us as 32 on those tiles
+// and one, 477 as 16 + 16 + 1.  (Counting the last launch as a full one refused that, and 20 layers of 1153 tokens of 2112 onto 640
+// went out as one launch of 300 workgroups: 117.5 us, as 16 of 320 tokens and 4 111.)
 inline int plan_layers(const RestoreArgs& a, int n_layers, Route& route) {
   const int per = layers_per_launch(2 * a.d_kv_pad / kTileF, (a.n_tok + kTileT - 1) / kTileT, n_layers);
-  const int n = per < n_layers ? per : n_layers;
+  int n = per < n_layers ? per : n_layers;
   route = restore_route(a, n);
   if (a.split_force || a.mode == 2 || a.d_model < kWideMinModel || n == n_layers) return n;
-  int nb = 0;
-  wide_us(a.d_kv, a.d_model, a.n_tok, n, nb);
-  const int n_wide = wide_layers_per_launch(a.d_kv, a.n_tok, nb, n_layers);
-  if (n_wide <= n) return n;
-  const float us = wide_us(a.d_kv, a.d_model, a.n_tok, n_wide, nb);
-  if (us * ((n_layers + n_wide - 1) / n_wide) >= route.us * ((n_layers + n - 1) / n)) return n;
-  route = Route();
-  route.kind = Route::kWide;
-  route.nb = nb;
-  route.us = us;
-  return n_wide;
+  float call_us = -1.f;                                  // of the choice so far; worked out where it is asked for
+  auto last_us = [&](int per_launch) { const int rest = n_layers % per_launch; return rest ? restore_route(a, rest).us : 0.f; };
+  for (int b = 9; b <= 10; ++b) {
+    const int n_wide = wide_layers_per_launch(a.d_kv, a.n_tok, b, n_layers);
+    if (n_wide <= per) continue;
+    if (call_us < 0.f) call_us = route.us * (n_layers / n) + last_us(n);
+    const float us = kWideCallPromise * wide_us(a.d_kv, a.d_model, a.n_tok, n_wide, b), full_us = us * (n_layers / n_wide);
+    if (full_us >= call_us) continue;
+    const float t = full_us + last_us(n_wide);
+    if (t >= call_us) continue;
+    call_us = t;
+    n = n_wide;
+    route = Route();
+    route.kind = Route::kWide;
+    route.nb = b;
+    route.us = us;
+  }
+  return n;
 }
 // What a context's split mode asks of a launch: `several` layers in one launch never split, but they take
 // the 256 x 256 tiles too when split launches are asked for.

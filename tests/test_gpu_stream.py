@@ -16,10 +16,13 @@ def hc():
 
 WIDE = [                                               # tiles of 256 rows x 288 or 320 tokens
     (2048, 3, 192, 257, 20, 0, "rms", None, 288),      # padded K/V parts, pair groups that straddle the heads
-    (2112, 5, 64, 1153, 20, 1, "bias", None, 288),     # one token in the last tile; 66 steps: the ring ends elsewhere
+    (2112, 5, 64, 1153, 20, 1, "bias", None, 320),     # 16 layers and four on another kernel; 66 steps: the ring ends elsewhere
+    (2112, 9, 64, 257, 33, 1, "bias", None, 288),      # 32 layers and one on tiles with loader waves
     (2048, 3, 192, 289, 20, 2, "bias", None, 320),     # one token in the last block but one; no rotation
     (2112, 3, 192, 320, 20, 1, "rms", None, 320),      # a full tile
     (2112, 40, 128, 1601, 1, 0, "rms", 288, 288),
+    (2048, 51, 64, 2305, 1, 0, "bias", 288, 288),      # one token in the last tile
+    (4096, 8, 128, 257, 20, 0, "rms", None, 288),
     (2048, 64, 128, 1153, 1, 1, "bias", 320, 320),
 ]
 

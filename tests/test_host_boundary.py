@@ -526,6 +526,86 @@ int main() {
     assert out.returncode == 0, out.stdout
 
 
+def test_layers_per_launch_prices_the_last_launch(hc, tmp_path):
+    """plan_layers over layer counts that leave a remainder: by the rule's own estimates, the whole call (full launches and
+    the last one, which goes its own way) takes no longer than with any other count it weighs, and a launch on the tiles of
+    288 or 320 tokens fills at most one round."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src = tmp_path / "plan.cpp"
+    src.write_text("""
+#include <cstdio>
+#include "hcache_internal.h"
+using namespace hc;
+int main() {
+  int bad = 0, n_all = 0, n_wide = 0;
+  const int widths[][2] = {{4096, 1024}, {8192, 1024}, {2112, 320}, {5120, 640}, {4096, 4096}, {5120, 5120}};
+  for (auto& w : widths)
+    for (int layers : {9, 16, 20, 24, 33, 40, 48, 80})
+      for (int tok : {250, 257, 270, 288, 289, 300, 320, 321, 577, 600, 1100, 1153, 1601}) {
+        RestoreArgs a{};
+        a.d_model = w[0];
+        a.d_kv = w[1];
+        a.d_kv_pad = round_up(w[1], kPartAlign);
+        a.n_tok = tok;
+        set_split_rule(a, 1, nullptr, true);
+        Route route;
+        const int n = plan_layers(a, layers, route);
+        auto call_us = [&](float us, int per) { return us * (layers / per) + (layers % per ? restore_route(a, layers % per).us : 0.f); };
+        const float us = call_us(route.us, n);
+        int per = layers_per_launch(2 * a.d_kv_pad / kTileF, (tok + kTileT - 1) / kTileT, layers);
+        if (per > layers) per = layers;
+        float least = call_us(restore_route(a, per).us, per);
+        for (int b = 9; b <= 10; ++b) {
+          int nb = b;
+          const int wide = wide_layers_per_launch(a.d_kv, tok, nb, layers);
+          if (wide <= per) continue;
+          const float t = call_us(kWideCallPromise * wide_us(a.d_kv, a.d_model, tok, wide, nb), wide);
+          if (t < least) least = t;
+        }
+        const int tiles = 2 * a.d_kv_pad / kTileF * ((tok + 32 * route.nb - 1) / (32 * (route.nb > 0 ? route.nb : 1)));
+        const bool over = route.kind == Route::kWide && n > per && tiles * n > kChipCUs;
+        if (us > 1.0001f * least || over) {
+          ++bad;
+          std::printf("%d onto %d, %d layers of %d: %d a launch, kernel %d x %d, %.1f us, least %.1f\\n", w[0], 2 * w[1], layers, tok, n, route.kind, route.nb, us, least);
+        }
+        ++n_all;
+        n_wide += n > per;
+      }
+  std::printf("%d of %d\\n", bad, n_all);
+  return bad != 0 || n_wide < 20;
+}
+""")
+    inc = [os.path.join(ROOT, "include"), os.path.join(ROOT, "paper_2410_05004_amd", "csrc")]
+    exe = tmp_path / "plan"
+    subprocess.run([hipcc, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-I", inc[0], "-I", inc[1],
+                    str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+
+
+# Measured on MI355X, one call over and over: (d_model, d_kv, tokens, layers in the call, {layers in the first launch: us}), the 256-token
+# tiles or those of 64 n tokens up to 16 layers, those of 288 or 320 tokens beyond, or where they fill a round with fewer
+WHOLE_CALL_TIMES = [
+    (4096, 1024, 257, 20, {20: 125.1, 16: 157.5}), (4096, 1024, 320, 20, {20: 136.2, 16: 163.8}),
+    (8192, 1024, 288, 20, {20: 232.5, 16: 294.7}), (8192, 1024, 320, 20, {20: 256.9, 16: 300.2}),
+    (4096, 1024, 320, 24, {24: 151.4, 16: 185.7}), (8192, 1024, 300, 24, {24: 275.7, 16: 333.0}),
+    (8192, 1024, 257, 33, {16: 477.4, 32: 337.3}), (4096, 1024, 300, 40, {16: 306.5, 32: 247.3}),
+    (8192, 1024, 289, 80, {16: 1123.1, 32: 896.6}), (5120, 640, 257, 48, {16: 356.2, 32: 283.7}),
+    (5120, 640, 289, 33, {24: 227.7, 32: 211.6}), (4096, 1024, 600, 16, {8: 192.7, 16: 158.4}),
+    (8192, 1024, 577, 80, {8: 1846.0, 16: 1463.4}), (5120, 640, 1153, 20, {10: 560.0, 12: 434.3}),
+    (2112, 320, 1153, 20, {20: 117.5, 16: 111.1}), (2112, 320, 577, 33, {24: 120.5, 32: 102.5}),
+]
+
+
+def test_whole_calls_against_measured_times(hc):
+    """Layers in the first launch of calls that leave a remainder: the count that was measured fastest."""
+    for d_model, d_kv, n_tok, n_layers, us in WHOLE_CALL_TIMES:
+        n = hc.diag_route(d_model, d_kv, n_tok, n_layers)[3]
+        assert n in us and us[n] == min(us.values()), (d_model, d_kv, n_tok, n_layers, n, us)
+
+
 # Measured on MI355X, weights not lately read: (d_model, d_kv, tokens, layers in the call or 0 for a single-layer call,
 # LayerNorm, us on the 256 x 256 tiles (whole or split), [us on tiles of 128 rows x 64, 128, .. 320 tokens])
 ROWS128_TIMES = [
