@@ -393,7 +393,8 @@ hc_status hc_set_loader(hc_ctx* ctx, int32_t mode);
  * second launch adds the shares up in a fixed order and finishes them (normalisation, RoPE,
  * scatter).  Results are deterministic and within the same tolerance, but not bit-identical to
  * an unsplit launch (fp32 summation order).  Split launches of one context are ordered after
- * each other through an event, whatever their streams.  mode 0: never split.  mode 2: split
+ * each other through an event, whatever their streams; of long LayerNorm launches, whose sums go to one of four
+ * slots in turn, each is ordered after the fourth before it (not under stream capture).  mode 0: never split.  mode 2: split
  * whenever the shape allows it (tests and measurements), and 256 x 256 tiles in every launch.
  * Launches over several layers (hc_restore_kv_layers) never split.  In mode 1 a layer of d_model >= 1024 and few tokens goes to
  * a kernel of its own when that is estimated faster than whole or split tiles (up to some 1500 to 2000 tokens
@@ -424,7 +425,9 @@ hc_status hc_diag_tile(int32_t d_model, int32_t d_kv, int32_t n_tok, int32_t n_l
  * Average duration in milliseconds of the restoration kernel launches (one per layer, or
  * one per group of layers under hc_restore_kv_layers) queued on
  * `stream` between hc_timing_begin and hc_timing_end, measured with HIP events on that
- * stream around every launch of this context (at most 4096 launches are recorded).
+ * stream around every launch of this context (at most 4096 launches are recorded).  A launch that
+ * works LayerNorm's sums out ahead counts that kernel in, a split launch both of its; the time a launch
+ * waits for an earlier one of the context on another stream (hc_set_split) is not counted.
  * hc_timing_end synchronises the stream.  *out_launches receives the launch count. */
 hc_status hc_timing_begin(hc_ctx* ctx);
 hc_status hc_timing_end(hc_ctx* ctx, void* stream, double* out_avg_ms, int32_t* out_launches);

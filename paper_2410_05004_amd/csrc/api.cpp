@@ -85,7 +85,8 @@ static int layer_mode(const hc_ctx* ctx, const hc_layer_state& L) {
   return ctx->desc.norm_kind == HC_NORM_LAYER ? 2 : (L.affine ? 1 : 0);
 }
 
-// One timed (when timing is on) launch.
+// One timed (when timing is on) launch.  What it waits for on account of another launch of the context (the slot of the tokens'
+// sums, the split workspace) lies ahead of the first event; the launch that works the sums out is part of the time.
 static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, const Route& route, LayerBatch* batch, int n_layers,
                               hipStream_t stream) {
   const bool timed = ctx->timing && ctx->ev_used + 2 <= 8192;
@@ -95,31 +96,33 @@ static hc_status timed_launch(hc_ctx* ctx, const RestoreArgs& a, const Route& ro
       HC_HIP(hipEventCreate(&e));
       ctx->ev_pool.push_back(e);
     }
-    HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used], stream));
   }
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (route.sums_ahead) HC_HIP(hipStreamIsCapturing(stream, &capturing));
-  if (route.sums_ahead && capturing == hipStreamCaptureStatusNone) {   // a captured launch must not wait for an event of the outside
-    std::lock_guard<std::mutex> lock(ctx->sums_mutex);
-    const int slot = ctx->sums_next;
+  const bool ahead = route.sums_ahead && capturing == hipStreamCaptureStatusNone;   // a captured launch must not wait for an event of the outside
+  std::unique_lock<std::mutex> lock(ctx->sums_mutex, std::defer_lock);
+  int slot = 0;
+  if (ahead) {
+    lock.lock();
+    slot = ctx->sums_next;
     ctx->sums_next = (slot + 1) % kSumsSlots;
-    float2* sums = ctx->sums + slot * kSumsTokens;
-    RestoreArgs b = a;
-    b.token_sums = sums;
     HC_HIP(hipStreamWaitEvent(stream, ctx->sums_done[slot], 0));
-    HC_HIP(launch_token_sums(a, batch, n_layers, sums, stream));
-    HC_HIP(launch_restore(b, route, batch, n_layers, stream));
-    HC_HIP(hipEventRecord(ctx->sums_done[slot], stream));
-    if (timed) {
-      HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used + 1], stream));
-      ctx->ev_used += 2;
-    }
-    return HC_OK;
   }
   // the workspace is one per context: a split launch waits for the one before it, whatever its stream
   if (route.split) HC_HIP(hipStreamWaitEvent(stream, ctx->split_done, 0));
-  HC_HIP(launch_restore(a, route, batch, n_layers, stream));
-  if (route.split) HC_HIP(hipEventRecord(ctx->split_done, stream));
+  if (timed) HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used], stream));
+  if (ahead) {
+    RestoreArgs b = a;
+    float2* sums = ctx->sums + slot * kSumsTokens;
+    b.token_sums = sums;
+    hipError_t e = launch_token_sums(a, batch, n_layers, sums, stream);
+    if (e == hipSuccess) e = launch_restore(b, route, batch, n_layers, stream);
+    HC_HIP(hipEventRecord(ctx->sums_done[slot], stream));   // also behind a launch that failed: what there is of it writes the slot
+    if (e != hipSuccess) return fail_hip(e, "launch with LayerNorm's sums ahead");
+  } else {
+    HC_HIP(launch_restore(a, route, batch, n_layers, stream));
+    if (route.split) HC_HIP(hipEventRecord(ctx->split_done, stream));
+  }
   if (timed) {
     HC_HIP(hipEventRecord(ctx->ev_pool[ctx->ev_used + 1], stream));
     ctx->ev_used += 2;

@@ -74,3 +74,60 @@ def test_sums_ahead_equal_sums_in_the_tiles(d_model, n_kv, n_tok, layers, style)
         check()
     assert ctx.poll_device_error(s) == 0
     ctx.destroy()
+
+
+def _context(hc, d_model, n_kv, n_tok, layers, norm_kind):
+    import torch
+    hd, B = 128, 16
+    ctx, s = hc.Context(gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                                     max_position=n_tok, rope_style=0, norm_kind=norm_kind)), gh.stream_handle()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    n_blocks, pools = -(-n_tok // B), []
+    w, gain = torch.randn((2 * n_kv * hd, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+    for l in range(layers):
+        if norm_kind:
+            ctx.set_layer_weights_affine(l, w, gain, 0.1 * gain, None, s)
+        else:
+            ctx.set_layer_weights(l, w, gain, s)
+        pools.append(torch.zeros((n_blocks + 2, 2, B, n_kv, hd), **bf))
+        ctx.set_kv_pool(l, pools[l], n_blocks + 2)
+    pos = torch.arange(n_tok, dtype=torch.int32, device="cuda")
+    table = torch.randperm(n_blocks + 2, device="cuda")[:n_blocks].to(torch.int32)
+    torch.cuda.synchronize()
+    return ctx, pools, pos, table, n_blocks
+
+
+@pytest.mark.parametrize("d_model,n_kv,n_tok,norm_kind,mode,what", [
+    (2048, 64, 8190, 1, 1, "sums"),        # the slots of the sums
+    (4096, 8, 300, 0, 2, "split"),         # the workspace of split launches
+])
+def test_timing_leaves_out_the_wait_for_another_stream(d_model, n_kv, n_tok, norm_kind, mode, what):
+    """The time of a launch that waits on the GPU for launches of the same context on another stream: at most that of the
+    launches which may share the chip with it (four and itself), not of the whole queue."""
+    import torch
+    import paper_2410_05004_amd as hc
+    assert hc.diag_tile(d_model, n_kv * 128, n_tok, 0, norm_kind, mode)[3] == (what == "sums")
+    assert (hc.diag_route(d_model, n_kv * 128, n_tok, 0, norm_kind, mode)[2] > 1) == (what == "split")
+    torch.manual_seed(1)
+    ctx, pools, pos, table, n_blocks = _context(hc, d_model, n_kv, n_tok, 1, norm_kind)
+    ctx.set_split(mode)
+    x = torch.randn((n_tok, d_model), dtype=torch.bfloat16, device="cuda")
+    main, side = gh.stream_handle(), torch.cuda.Stream()
+    call = lambda stream: ctx.restore_kv(0, x, pos, n_tok, table, n_blocks, stream)
+    for _ in range(20):
+        call(main)
+    torch.cuda.synchronize()
+    ctx.timing_begin()
+    for _ in range(20):
+        call(main)
+    alone = ctx.timing_end_stats(main)[2]
+    torch.cuda.synchronize()
+    for _ in range(60):
+        call(side.cuda_stream)
+    ctx.timing_begin()
+    call(main)
+    behind, launches = ctx.timing_end(main)
+    torch.cuda.synchronize()
+    assert launches == 1
+    assert behind < 8 * alone, (behind, alone)
+    ctx.destroy()
