@@ -131,3 +131,38 @@ def test_timing_leaves_out_the_wait_for_another_stream(d_model, n_kv, n_tok, nor
     assert launches == 1
     assert behind < 8 * alone, (behind, alone)
     ctx.destroy()
+
+
+def test_slots_of_the_sums_hold_until_their_readers_are_done():
+    """Sixteen calls in flight on two streams, four times as many as there are slots, each with hidden states, a layer and a pool of
+    its own: every pool gets its own call's results.  The inputs differ in scale and offset, so another call's sums would show
+    in every value."""
+    import torch
+    import paper_2410_05004_amd as hc
+    d_model, n_kv, n_tok, layers = 2048, 64, 8190, 8
+    assert hc.diag_tile(d_model, n_kv * 128, n_tok, 0, 1)[3] == 1
+    torch.manual_seed(2)
+    ctx, pools, pos, table, n_blocks = _context(hc, d_model, n_kv, n_tok, layers, 1)
+    xs = [(torch.randn((n_tok, d_model), device="cuda") * (1 + 0.5 * l) + 0.25 * l).to(torch.bfloat16) for l in range(layers)]
+    for l in range(layers):
+        gh.restore_whole_tiles(ctx, l, xs[l], pos, n_tok, table, n_blocks, gh.stream_handle())
+    torch.cuda.synchronize()
+    want = [p.clone() for p in pools]
+    sums = [(x.double().square().sum(1), x.double().sum(1)) for x in xs]
+    for l in range(1, layers):                             # another call's sums are others by far, for nearly every token
+        assert all(((a - b).abs() > 0.05 * b.abs().mean()).float().mean() > 0.8 for a, b in zip(sums[l], sums[l - 1]))
+        assert not torch.equal(want[l], want[l - 1])
+    ctx.set_split(1)
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    for _ in range(3):
+        for p in pools:
+            p.zero_()
+        torch.cuda.synchronize()
+        for i in range(2 * layers):                        # a layer stays on its stream
+            l = i % layers
+            ctx.restore_kv(l, xs[l], pos, n_tok, table, n_blocks, streams[l % 2].cuda_stream)
+        torch.cuda.synchronize()
+        for l in range(layers):
+            assert torch.equal(pools[l].view(torch.int16), want[l].view(torch.int16)), l
+    assert ctx.poll_device_error(gh.stream_handle()) == 0
+    ctx.destroy()
