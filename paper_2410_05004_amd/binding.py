@@ -134,7 +134,8 @@ def diag_split_plan(d_model, d_kv, n_tok, mode=1):
 
 def diag_route(d_model, d_kv, n_tok, n_layers=0, norm_kind=HC_NORM_RMS, mode=1):
     """hc_diag_route: (kernel "tiles" | "few" | "rows128", token blocks per workgroup, workgroups per split
-    tile, layers in the launch)."""
+    tile, layers in the launch).  "rows128" stands for every kernel of other tiles than 256 x 256, those with loader waves and
+    those of 256 rows among them, its blocks for 64 tokens, rounded up: diag_tile has the tile itself."""
     out = (C.c_int32 * 4)()
     _check(lib.hc_diag_route(d_model, d_kv, n_tok, n_layers, norm_kind, mode, out))
     return (("tiles", "few", "rows128")[out[0]], out[1], out[2], out[3])

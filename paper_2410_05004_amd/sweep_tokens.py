@@ -7,7 +7,7 @@ script measures the same curve for this library's kernel on MI355X: time per lau
 n_tok = step, 2*step, ... at a given model shape, so that a scheduler can pick mini-batch
 sizes on the flat part of each step (the large tiles are 256 tokens).  Every token count is
 timed as the library launches it (hc_set_split mode 1: the kernel that a cost model says is
-fastest, hc_diag_route), on whole tiles of 256 features x 256 tokens (mode 2 and
+fastest, hc_diag_route and hc_diag_tile), on whole tiles of 256 features x 256 tokens (mode 2 and
 hc_restore_kv_layers over one layer, which never splits), and on these tiles with a partly filled
 last round of workgroups split along d_model, where the shape allows it (mode 2).
 
@@ -25,6 +25,14 @@ import numpy as np
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
+
+
+def kernel_name(hc, d_model, d_kv, n_tok, norm_kind):
+    """The kernel that a single-layer call takes, with its tile."""
+    kernel, blocks, ways, _ = hc.diag_route(d_model, d_kv, n_tok, 0, norm_kind)
+    rows, tokens, loaders, _ = hc.diag_tile(d_model, d_kv, n_tok, 0, norm_kind)
+    return {"tiles": "split tiles" if ways > 1 else "whole tiles", "few": f"few tokens, {16 * blocks}",
+            "rows128": f"{rows} rows x {tokens}" + (", loader waves" if loaders else "")}[kernel]
 
 
 def main():
@@ -90,9 +98,7 @@ def main():
 
     for n in range(args.step, T + 1, args.step):
         plan = hc.diag_split_plan(w.d_model, w.d_kv, n, 2)
-        kernel, blocks, ways, _ = hc.diag_route(w.d_model, w.d_kv, n, 0, 1 if layer_norm else 0)
-        name = {"tiles": "split tiles" if ways > 1 else "whole tiles", "few": f"few tokens, {16 * blocks}",
-                "rows128": f"128 rows x {64 * blocks}"}[kernel]
+        name = kernel_name(hc, w.d_model, w.d_kv, n, 1 if layer_norm else 0)
         us0 = timed(n, 2, whole=True)
         us2 = timed(n, 2) if plan["split"] else None
         us = timed(n, 1)

@@ -643,14 +643,19 @@ def test_tiles_of_128_rows_only_where_they_were_measured_faster(hc):
     for d_model, d_kv, n_tok, n_layers, norm, tiles_us, rows_us in ROWS128_TIMES:
         kernel, blocks, _, _ = hc.diag_route(d_model, d_kv, n_tok, n_layers, norm)
         assert kernel != "few"
+        rows, tokens, loaders, _ = hc.diag_tile(d_model, d_kv, n_tok, n_layers, norm)
+        if loaders or (rows, tokens) in ((256, 288), (256, 320)):   # kernels of their own: with their times in TILE_TIMES
+            assert (d_model, d_kv, n_tok, n_layers, norm) in [r[:5] for r in TILE_TIMES]
+            continue
+        assert (rows, tokens) == ((256, 256) if kernel == "tiles" else (128, 64 * blocks))
         us = tiles_us if kernel == "tiles" else rows_us[blocks - 1]
         where = (d_model, d_kv, n_tok, n_layers, norm, kernel, blocks, us, tiles_us, rows_us)
         assert us <= 1.05 * tiles_us, where
         assert min(rows_us) > 0.7 * tiles_us or us <= 1.1 * min(rows_us), where
 
 
-# Measured on MI355X: (d_model, d_kv, tokens, layers in the call or 0, LayerNorm, {(rows, tokens, loader waves) of a tile: us}), a single
-# layer with the weights from memory, several over and over
+# Measured on MI355X: (d_model, d_kv, tokens, layers in the call or 0, LayerNorm, {(rows, tokens, loader waves) of a tile: us}), the kernels of
+# a row on one machine; 256 x 256 tiles whole or split; a single layer mostly with the weights from memory, several mostly over and over
 TILE_TIMES = [
     (4224, 3584, 853, 0, 0, {(128, 96, 4): 86.8, (128, 256, 0): 66.9}),      # nine token tiles: the weights into the L2s nine times
     (4864, 2816, 993, 0, 0, {(128, 96, 4): 97.7, (128, 256, 0): 81.4}),
@@ -664,6 +669,12 @@ TILE_TIMES = [
     (5120, 5120, 161, 3, 0, {(128, 192, 4): 118.5, (256, 256, 0): 106.0}),
     (5120, 5120, 120, 4, 0, {(128, 128, 4): 120.1, (128, 128, 0): 128.8}),
     (4096, 1024, 2501, 0, 0, {(128, 160, 4): 48.1, (128, 192, 0): 54.4}),
+    (4800, 576, 765, 3, 0, {(128, 64, 4): 74.4, (128, 64, 0): 76.7, (256, 256, 0): 92.9}),
+    (1600, 768, 5, 4, 0, {(128, 64, 4): 14.3, (128, 64, 0): 20.95, (256, 256, 0): 33.3}),
+    (5120, 5120, 1601, 0, 0, {(256, 288, 0): 147.5, (256, 256, 0): 163.5}),
+    (4096, 1024, 300, 32, 0, {(256, 320, 0): 185.0, (256, 256, 0): 247.0}),
+    (4096, 4096, 277, 8, 0, {(256, 288, 0): 148.0, (256, 256, 0): 213.4, (128, 160, 4): 203.0}),
+    (4096, 1024, 1128, 8, 0, {(256, 288, 0): 139.5, (128, 192, 4): 137.0, (256, 256, 0): 178.4}),
 ]
 
 
@@ -674,5 +685,13 @@ def test_tiles_with_loader_waves_only_where_they_were_measured_faster(hc):
         tile = hc.diag_tile(d_model, d_kv, n_tok, n_layers, norm)[:3]
         best = min(us.values())
         assert tile not in us or us[tile] <= 1.05 * best, (d_model, d_kv, n_tok, n_layers, norm, tile, us)
-        # a tile that is not in the row is no tile with loader waves, which are measured at each of their widths
         assert tile in us or tile[2] == 0, (d_model, d_kv, n_tok, n_layers, norm, tile, us)
+
+
+def test_token_sweep_names_the_tile_of_a_launch(hc):
+    """sweep_tokens prints the tile that runs: 128 rows with and without loader waves, 256 rows of more than 256 tokens."""
+    from paper_2410_05004_amd.sweep_tokens import kernel_name
+    for shape, name in (((4096, 1024, 37, 0), "few tokens, 16"), ((4096, 1024, 2501, 0), "128 rows x 160, loader waves"),
+                        ((5120, 5120, 1601, 0), "256 rows x 288"), ((704, 576, 1601, 0), "128 rows x 128"),
+                        ((4096, 1024, 8192, 0), "whole tiles")):
+        assert kernel_name(hc, *shape) == name, (shape, kernel_name(hc, *shape))
