@@ -142,3 +142,74 @@ def test_last_tile_of_few_tokens_costs_no_more_than_a_full_one(hc):
     few, full = (sorted(us[n][2:])[2] for n in (65, 128))
     assert few < 1.15 * full, us
     ctx.destroy()
+
+
+@pytest.mark.parametrize("d_model,n_kv,hd,n_tok,layers,style,norm,tile", [
+    (1152, 5, 64, 1025, 1, 0, "layer", (128, 64, 4, 0)),
+    (1152, 8, 192, 801, 4, 1, "rms", (128, 160, 4, 0)),
+    (2048, 51, 64, 2305, 1, 0, "bias", (256, 288, 0, 0)),
+    (2112, 3, 192, 320, 20, 1, "rms", (256, 320, 0, 0)),
+    (2048, 64, 128, 4097, 2, 0, "layer", (256, 256, 0, 1)),    # sums ahead of the tiles
+])
+def test_infinities_nan_and_unmapped_pages(hc, d_model, n_kv, hd, n_tok, layers, style, norm, tile):
+    """Token rows with infinities, NaN, zeros, values whose squares overflow and the smallest ones, first and last of the tokens
+    among them, and an unmapped (-1) page: the 256 x 256 tiles' results and flags, and no trace in any other token."""
+    import torch
+    assert hc.diag_tile(d_model, n_kv * hd, n_tok, layers if layers > 1 else 0, norm == "layer") == tile
+    torch.manual_seed(n_tok)
+    bf, B = dict(dtype=torch.bfloat16, device="cuda"), 16
+    ctx, s = hc.Context(gh.make_desc(hc, n_layers=layers, d_model=d_model, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, block_size=B,
+                                     max_position=n_tok, rope_style=style, norm_kind=int(norm == "layer"))), gh.stream_handle()
+    rows, n_blocks = 2 * n_kv * hd, -(-n_tok // B)
+    num_pages = n_blocks + 2
+    keep, pools, xs, clean = [], [], [], []
+    bad = [0, 3, 17, 40, 100, n_tok // 2, n_tok - 1]
+    for l in range(layers):
+        w, gain = torch.randn((rows, d_model), **bf) * 0.05, 1 + 0.1 * torch.randn(d_model, **bf)
+        shift = 0.1 * torch.randn(d_model, **bf) if norm == "layer" else None
+        bias = 0.1 * torch.randn(rows, **bf) if norm != "rms" else None
+        keep += [w, gain, shift, bias]
+        if norm == "rms":
+            ctx.set_layer_weights(l, w, gain, s)
+        else:
+            ctx.set_layer_weights_affine(l, w, gain, shift, bias, s)
+        pools.append(gh.new_pool(num_pages, B, n_kv, hd))
+        ctx.set_kv_pool(l, pools[l], num_pages)
+        clean.append(torch.randn((n_tok, d_model), **bf) + 0.25)
+        x = clean[l].clone()
+        x[bad[0], 5], x[bad[1], d_model - 1], x[bad[2], 64] = float("inf"), float("-inf"), float("nan")
+        x[bad[3]], x[bad[4]], x[bad[5]] = 0, 3e38, 1e-39
+        x[bad[6], 7] = float("nan")
+        xs.append(x)
+    pos = torch.arange(n_tok, dtype=torch.int32, device="cuda")
+    table = torch.randperm(num_pages, device="cuda")[:n_blocks].to(torch.int32)
+    table[n_blocks // 3] = -1
+    page = table.cpu().numpy()[np.arange(n_tok) // B]
+
+    def outcome(inputs, whole):
+        for p in pools:
+            p.view(torch.int16).fill_(np.array(gh.SENTINEL, dtype=np.uint16).view(np.int16).item())
+        ctx.set_split(2 if whole else 1)
+        if whole:
+            for l in range(layers):
+                gh.restore_whole_tiles(ctx, l, inputs[l], pos, n_tok, table, n_blocks, s)
+        elif layers > 1:
+            ctx.restore_kv_layers(0, inputs, pos, n_tok, table, n_blocks, s)
+        else:
+            ctx.restore_kv(0, inputs[0], pos, n_tok, table, n_blocks, s)
+        return ctx.poll_device_error(s), [gh.pool_bits(p) for p in pools]
+
+    flags, want = outcome(xs, True)
+    got_flags, got = outcome(xs, False)
+    _, ref = outcome(clean, False)
+    assert flags == got_flags == hc.HC_DEV_BAD_PAGE
+    nan = lambda b: (b & 0x7FFF) > 0x7F80
+    fine = np.array([t for t in range(n_tok) if t not in bad and page[t] >= 0])
+    for g, b, r in zip(got, want, ref):
+        assert np.array_equal(nan(g), nan(b)) and np.array_equal(g[~nan(g)], b[~nan(b)])
+        at = page[fine], slice(None), fine % B
+        assert np.array_equal(g[at], r[at]) and not nan(g[at]).any()
+        assert nan(g[page[bad[2]], :, bad[2] % B]).all()
+        if norm == "rms" and page[bad[3]] >= 0:
+            assert not (g[page[bad[3]], :, bad[3] % B] & 0x7FFF).any()   # zeros stay zeros
+    ctx.destroy()
