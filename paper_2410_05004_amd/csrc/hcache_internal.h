@@ -286,9 +286,9 @@ constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token ker
 // 2000 of two to eight layers (9 %): rounds as above, of step us per 64 channels, growing with nb and with how many of the
 // CUs are busy (the clock falls), `more` of it for every further round of several layers, whose CUs have lost step; the
 // hypotenuse of that and the operands' time from memory (the hidden states count 2.4 times: several XCDs fetch them).
-// Over those shapes, time under this rule against the one without these tiles (weights from memory where three copies of
-// the layer do not fit the caches): single layers 0.944 in the geometric mean (0.931 if every choice were the fastest), 6 of
-// 2000 more than 4 % slower, 610 faster; several layers (485 of 2000 take these tiles) 0.925, 5 and 465.
+// Over 2411 single-layer shapes and 2246 calls of two to four layers, each measured on every kernel, time under this rule against the
+// one without these tiles: single layers 0.937 in the geometric mean (0.923 if every choice were the fastest), 4 more than 4 %
+// slower; of the calls 1438 take these tiles, to 0.751, 18.
 // Where the lines lie:
 //  * d_model above 1024: below, up to 16 supersteps, a launch is mostly prologue, epilogue and its issue, and these tiles gain
 //    a microsecond or two (700 shapes: 0.92 of the time in the median up to 256 channels, 0.87 at 512 .. 1024, 0.82 above);
