@@ -287,7 +287,7 @@ constexpr float kFewWeightsUsPerByte = 1.f / 5.4e6f;     // as the few-token ker
 // CUs are busy (the clock falls), `more` of it for every further round of several layers, whose CUs have lost step; the
 // hypotenuse of that and the operands' time from memory (the hidden states count 2.4 times: several XCDs fetch them).
 // Over 2411 single-layer shapes and 2246 calls of two to four layers, each measured on every kernel, time under this rule against the
-// one without these tiles: single layers 0.937 in the geometric mean (0.923 if every choice were the fastest), 4 more than 4 %
+// one without these tiles: single layers 0.937 in the geometric mean (0.923 if every choice were the fastest), 5 more than 4 %
 // slower; of the calls 1438 take these tiles, to 0.751, 18.
 // Where the lines lie:
 //  * d_model above 1024: below, up to 16 supersteps, a launch is mostly prologue, epilogue and its issue, and these tiles gain
@@ -321,13 +321,14 @@ constexpr float kStreamColdRounds = 1.2f, kLastCacheBytes = 2.56e8f;
 
 // Least time of a launch of nf x nt tiles of 128 rows: that of filling the L2s (all layers' bytes).  Every super tile brings its rows of
 // the weights into its XCD's L2, but for those that an XCD works on at once and that lie in one column (k and k + 8 do where 8 is a
-// multiple of the columns), and the hidden states come into the L2 of each XCD that has a column.  6.6 TB/s and 3.5 us, fitted on the
-// tiles with loader waves of 9925 launches: those that this bounds were estimated 24 % too low without it and are 2 % with it
+// multiple of the columns), and the hidden states come into the L2 of each XCD that has a column.  6.6 TB/s and 2.5 us, fitted on the
+// tiles with loader waves of 9925 launches: those that this bounds were estimated 25 % too low without it and are 3 % with it
 // (7 % rms).  Super tiles of one token tile each, taken because no other shape fits the XCDs evenly, are the usual case: 853
 // tokens of 4224 channels onto 7168 in nine tiles of 96 tokens bring in the weights nine times, 545 MB: 86 us, 65 in tiles of 64 n
-// tokens.  Of 2411 single-layer shapes 94 go elsewhere by it, to 0.88 of the time, 3 of them more than 4 % slower.  No
-// estimate of a kernel, so no promise on top.  Up to 1024 channels nothing was measured against it.
-constexpr float kL2FillUsPerByte = 1.f / 6.6e6f, kL2FillUs = 3.5f;
+// tokens.  Of 2411 single-layer shapes 76 go elsewhere by it, to 0.85 of the time, none more than 4 % slower in the mean of
+// weights from memory and from the caches (with 3.5 us it is 94, 0.88 and 3, and 257 to 320 tokens of 5120 onto 10240 lose up to 14 %
+// from memory).  No estimate of a kernel, so no promise on top.  Up to 1024 channels nothing was measured against it.
+constexpr float kL2FillUsPerByte = 1.f / 6.6e6f, kL2FillUs = 2.5f;
 inline float l2_fill_us(int nf, int nt, float weights, float hidden, float out) {
   TileGrid g;
   choose_tile_grid(nf, nt, g);
